@@ -281,12 +281,19 @@ def work(case):
 
 
 def tolerance(case):
-    # fp32 layers: fp32 sums in another order (1e-7 to 3e-7 seen).  bf16
-    # layers: the rounding of the outputs to bf16 (1.7e-3) and of the fp16
-    # intermediates, and one or two tokens whose similarity ties with the
-    # threshold to the last bits, whose rows then hold the previous step's
-    # output (2% away) and whose keys come or go.
-    return {"rel": 1e-5} if case["dtype"] == "f32" else {"rel": 1e-2}
+    # fp32 layers: fp32 sums in another order (4e-7 to 8e-7 from 64 bits)
+    if case["dtype"] == "f32":
+        return {"rel": 1e-5}
+    # bf16: the rounding of the outputs and of the fp16 intermediates (1.7e-3
+    # from 64 bits)
+    rounding = {"rel": 8e-3}
+    if case["kind"] in ("full", "ffn") or case["gran"] in ("frame", "block"):
+        return rounding
+    # Token Cache: besides, two tokens whose similarities tie at the threshold
+    # to the last bits may trade places.  One such swap was measured at 0.6e-2
+    # (4096 tokens) to 1.6e-2 (1024 tokens), with differences up to 0.93 of
+    # the outputs' root mean square in the swapped rows
+    return {"rel": 2e-2, "max": 0.95}
 
 
 # ---------------------------------------------------------------------------
