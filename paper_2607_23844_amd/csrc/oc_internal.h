@@ -110,6 +110,9 @@ inline MatchSplit match_split(const Plan &p) {
     const long target = 256 / tiles;
     int sps = (int)((nk + target - 1) / target);   // 64-steps per split
     const int per_seg = seg > 0 ? seg / 64 : nk;
+    // a split stays inside one segment: a whole segment is the longest one
+    // (many frames over a middling number of tiles ask for more)
+    if (sps > per_seg) sps = per_seg;
     while (per_seg % sps != 0 || nk % sps != 0) ++sps;
     if (nk / sps < 2) return m;
     m.n_split = nk / sps;
