@@ -629,6 +629,7 @@ static hipError_t go_dh(const Plan &p, const AttnArgs &a, int Lk, hipStream_t st
 
 hipError_t launch_flash(const Plan &p, const AttnArgs &a, int Lk, hipStream_t st) {
     StageScope _stage(st, "flash");
+    if (flash_splits(p, a, Lk)) return launch_flash_split(p, a, Lk, st);
     switch (p.dh) {
         case 16: return go_dh<16>(p, a, Lk, st);
         case 32: return go_dh<32>(p, a, Lk, st);

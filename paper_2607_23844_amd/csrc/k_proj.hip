@@ -44,8 +44,7 @@ namespace oc {
 // sequence (a single sequence, or L % 128 == 0) are written as Vt rows:
 // the positions of the tile's tokens, zero for positions past the end (the
 // key padding up to lpad), in whole chunks.  Otherwise elements are stored
-// one by one and, when the attention kernel needs it, the key padding is
-// zeroed separately.  The DMA engine runs double-buffered (two blocks per
+// one by one and the key padding is zeroed separately.  The DMA engine runs double-buffered (two blocks per
 // CU).
 // ---------------------------------------------------------------------------
 // Tile shapes (SH): 0 = 128 x 128; 1 = 192 x 128 (192 rows of the A side:
@@ -70,7 +69,7 @@ template <bool DMA, int SH, bool VARLEN>
 __global__ __launch_bounds__(256) void k_proj_qkv(RowMap rm, const uint16_t *__restrict__ wq,
                                                   const uint16_t *__restrict__ wk, const uint16_t *__restrict__ wv,
                                                   int hd, int dh, float qscale, int nw, int n_qk_at, int n_bt,
-                                                  int n_v_at, int n_v_bt, int n_seq, int L, int lpad, int zero_pad,
+                                                  int n_v_at, int n_v_bt, int n_seq, int L, int lpad,
                                                   const int32_t *__restrict__ seq_off, uint16_t *__restrict__ Q,
                                                   uint16_t *__restrict__ K, uint16_t *__restrict__ Vt) {
     using T = QKVTile<DMA, SH>;
@@ -155,9 +154,9 @@ __global__ __launch_bounds__(256) void k_proj_qkv(RowMap rm, const uint16_t *__r
                 }
     }
     // zero the padded key positions [Lk, lpad) of this block's features, for
-    // the sequences s = at, at + n_v_at, ... (the DMA-staged attention reads them)
+    // the sequences s = at, at + n_v_at, ... (the attention reads them)
     const int npad = lpad - Lk;
-    if (!VARLEN && zero_pad && npad > 0) {
+    if (!VARLEN && npad > 0) {
         for (int sq = at; sq < n_seq; sq += n_v_at)
             for (int idx = threadIdx.x; idx < BB * npad; idx += blockDim.x) {
                 const int f = f0 + idx / npad, jj = Lk + idx % npad;
@@ -174,7 +173,7 @@ static long qkv_tiles(const Plan &p, int rows, int nw, int BA, int BB) {
 }
 
 template <bool DMA, int SH, bool VARLEN>
-static hipError_t launch_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a, float qscale, int nw, int zero_pad,
+static hipError_t launch_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a, float qscale, int nw,
                              hipStream_t st) {
     constexpr int BA = QKVShape<DMA, SH>::BA, BB = QKVShape<DMA, SH>::BB;
     const hipError_t e = allow_lds(k_proj_qkv<DMA, SH, VARLEN>, QKVTile<DMA, SH>::LDS_BYTES);
@@ -184,7 +183,7 @@ static hipError_t launch_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a,
     const int total = n_qk_at * n_bt + n_v_at * n_v_bt;
     launch_k(k_proj_qkv<DMA, SH, VARLEN>, total, 256, QKVTile<DMA, SH>::LDS_BYTES, st, rm, (const uint16_t *)a.wq,
              (const uint16_t *)a.wk, (const uint16_t *)a.wv, p.hd, p.dh, qscale, nw, n_qk_at, n_bt, n_v_at, n_v_bt,
-             a.n_seq, a.L, a.lpad, zero_pad, a.seq_off, (uint16_t *)a.q, (uint16_t *)a.k, (uint16_t *)a.vt);
+             a.n_seq, a.L, a.lpad, a.seq_off, (uint16_t *)a.q, (uint16_t *)a.k, (uint16_t *)a.vt);
     return hipGetLastError();
 }
 
@@ -192,8 +191,8 @@ static hipError_t launch_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a,
 // instance, so that the uniform kernels carry none of its code)
 template <bool V>
 static hipError_t launch_shape(const Plan &p, const RowMap &rm, const AttnArgs &a, float qscale, int nw,
-                               int zero_pad, hipStream_t st) {
-    if (p.C % 64 != 0) return launch_qkv<false, 0, V>(p, rm, a, qscale, nw, zero_pad, st);
+                               hipStream_t st) {
+    if (p.C % 64 != 0) return launch_qkv<false, 0, V>(p, rm, a, qscale, nw, st);
     // block rounds (two blocks per CU) times the work of one tile, a wide
     // tile being 1.5 units (the SD3-like layer at r = 0.5: 460 tiles of 192 x
     // 128 in one round, 44 us, against 684 of 128 x 128 in two, 51 us; one
@@ -206,9 +205,9 @@ static hipError_t launch_shape(const Plan &p, const RowMap &rm, const AttnArgs &
     const long c192a = 3 * ((qkv_tiles(p, rm.n_rows, nw, 192, 128) + slots - 1) / slots);
     const long c192b = 3 * ((qkv_tiles(p, rm.n_rows, nw, 128, 192) + slots - 1) / slots);
     const bool rows192 = nw == 3 || a.n_seq == 1 || a.L % 192 == 0;
-    if (rows192 && c192a < c128 && c192a <= c192b) return launch_qkv<true, 1, V>(p, rm, a, qscale, nw, zero_pad, st);
-    if (c192b < c128) return launch_qkv<true, 2, V>(p, rm, a, qscale, nw, zero_pad, st);
-    return launch_qkv<true, 0, V>(p, rm, a, qscale, nw, zero_pad, st);
+    if (rows192 && c192a < c128 && c192a <= c192b) return launch_qkv<true, 1, V>(p, rm, a, qscale, nw, st);
+    if (c192b < c128) return launch_qkv<true, 2, V>(p, rm, a, qscale, nw, st);
+    return launch_qkv<true, 0, V>(p, rm, a, qscale, nw, st);
 }
 
 hipError_t launch_proj_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a, hipStream_t st) {
@@ -218,11 +217,10 @@ hipError_t launch_proj_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a, h
     // sequences of varying length: Vt slots per sequence, filled element by
     // element; the attention masks their ends itself (no padding to zero)
     const bool varlen = a.seq_off != nullptr;
-    const int zero_pad = !varlen && flash_uses_dma(p.dh, Lk, p.hd) ? 1 : 0;
     // short sequences: V rows from the Q/K tiles (nw = 3), no V tiles
     const int nw = !varlen && attn_short(Lk) ? 3 : 2;
-    return varlen ? launch_shape<true>(p, rm, a, qscale, nw, zero_pad, st)
-                  : launch_shape<false>(p, rm, a, qscale, nw, zero_pad, st);
+    return varlen ? launch_shape<true>(p, rm, a, qscale, nw, st)
+                  : launch_shape<false>(p, rm, a, qscale, nw, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -70,8 +70,9 @@ __device__ __forceinline__ int vt_key_of_pos(int p) { return (p & ~12) | ((p & 4
 
 // Whether the attention kernel may stage K/V by DMA for this head dim and
 // key count (head dims that are not a multiple of 64 take it only for grids
-// of eight-wave blocks).  The DMA path relies on the V projection having
-// zeroed the padded key positions [Lk, lpad) of every Vt row.
+// of eight-wave blocks).  The attention relies on the V projection having
+// zeroed the padded key positions [Lk, lpad) of every Vt row (but for
+// sequences of varying length).
 // (buffer offsets of K are 32-bit: Lk * hd * 2 bytes must stay below 2^31)
 inline bool flash_uses_dma(int dh, int Lk, int hd) {
     return dh % 8 == 0 && dh <= 128 && Lk >= 256 && (long)Lk * hd * 2 < (1L << 31);
@@ -92,6 +93,10 @@ hipError_t launch_qkv_attn_short(const Plan &p, const RowMap &rm, const AttnArgs
 
 hipError_t launch_proj_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a, hipStream_t st);
 hipError_t launch_proj_out(const Plan &p, int n_rows, const AttnArgs &a, hipStream_t st);
+// Attention of few query tiles over long sequences: the waves of a block
+// share out the keys (k_flash_split.hip), where flash_splits says so
+bool flash_splits(const Plan &p, const AttnArgs &a, int Lk);
+hipError_t launch_flash_split(const Plan &p, const AttnArgs &a, int Lk, hipStream_t st);
 hipError_t launch_flash(const Plan &p, const AttnArgs &a, int Lk, hipStream_t st);
 
 }  // namespace oc
