@@ -43,8 +43,8 @@ namespace oc {
 // Vt[h][s][d][pos].  V tiles whose rows are a 16-aligned run of one
 // sequence (a single sequence, or L % 128 == 0) are written as Vt rows:
 // the positions of the tile's tokens, zero for positions past the end (the
-// key padding up to lpad), in whole chunks.  Otherwise elements are stored
-// one by one and the key padding is zeroed separately.  The DMA engine runs double-buffered (two blocks per
+// key padding up to lpad), in whole chunks.  Otherwise they are stored in
+// quads of tokens and the key padding is zeroed separately.  The DMA engine runs double-buffered (two blocks per
 // CU).
 // ---------------------------------------------------------------------------
 // Tile shapes (SH): 0 = 128 x 128; 1 = 192 x 128 (192 rows of the A side:
@@ -135,23 +135,40 @@ __global__ __launch_bounds__(256) void k_proj_qkv(RowMap rm, const uint16_t *__r
         });
         return;
     }
-#pragma unroll
-    for (int j = 0; j < T::TB; ++j) {
-        const int f = f0 + T::b_of(j);
-        if (f >= hd) continue;
+    // Tiles that cross sequences (or sequences whose starts are not multiples
+    // of the tile): staged as rows of features too, then stored in quads of
+    // tokens, lanes over consecutive tokens.  A quad inside one sequence that
+    // starts at a multiple of 4 is 8 contiguous bytes of a Vt row.  (Each lane
+    // storing its accumulators one by one, a stride of lpad apart, took 110 us
+    // for the whole launch on 16 frames of 16 x 16 tokens of 16 heads of 72
+    // that keep varying numbers of tokens; 41 us this way.)
+    stage_rows<BA>(t, lds, [](float v, int) { return f2h_bits(v); }, [](int a) { return a; });
+    int2 *const where = reinterpret_cast<int2 *>(lds + BB * (BA + 8));   // (sequence, position) per token
+    static_assert((size_t)BB * (BA + 8) * 2 + BA * sizeof(int2) <= T::LDS_BYTES, "token table fits in the ring");
+    for (int a = threadIdx.x; a < BA; a += 256) {
+        int s = -1, jj = 0;
+        if (r0 + a < rm.n_rows) seq_pos(r0 + a, n_seq, L, s, jj, VARLEN ? seq_off : nullptr);
+        where[a] = make_int2(s, jj);
+    }
+    __syncthreads();
+    constexpr int QPR = BA / 4;
+    for (int u = threadIdx.x; u < BB * QPR; u += 256) {
+        const int b = u / QPR, a = (u - b * QPR) * 4, f = f0 + b;
+        if (f >= hd) break;   // (b rises with u)
         const int h = f / dh, d = f - h * dh;
+        const uint16_t *src = lds + b * (BA + 8) + a;
+        uint16_t *const row = Vt + ((long)h * n_seq * dh + d) * lpad;   // sequence s: s * dh * lpad further
+        const int2 w0 = where[a], w3 = where[a + 3];
+        if (w0.x >= 0 && w0.x == w3.x && (w0.y & 3) == 0) {
+            *reinterpret_cast<u16x4 *>(row + (long)w0.x * dh * lpad + vt_key_of_pos(w0.y)) =
+                *reinterpret_cast<const u16x4 *>(src);
+        } else {
 #pragma unroll
-        for (int i = 0; i < T::TA; ++i)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int r = r0 + T::a_of(i, g) + e;
-                    if (r >= rm.n_rows) continue;
-                    int s, jj;
-                    seq_pos(r, n_seq, L, s, jj, VARLEN ? seq_off : nullptr);
-                    Vt[(((long)h * n_seq + s) * dh + d) * lpad + vt_key_of_pos(jj)] = f2h_bits(t.acc[i][j][4 * g + e]);
-                }
+            for (int e = 0; e < 4; ++e) {
+                const int2 w = where[a + e];
+                if (w.x >= 0) row[(long)w.x * dh * lpad + vt_key_of_pos(w.y)] = src[e];
+            }
+        }
     }
     // zero the padded key positions [Lk, lpad) of this block's features, for
     // the sequences s = at, at + n_v_at, ... (the attention reads them)
@@ -197,8 +214,8 @@ static hipError_t launch_shape(const Plan &p, const RowMap &rm, const AttnArgs &
     // tile being 1.5 units (the SD3-like layer at r = 0.5: 460 tiles of 192 x
     // 128 in one round, 44 us, against 684 of 128 x 128 in two, 51 us; one
     // round either way, or two either way, keeps the smaller tiles).  192-row
-    // V tiles must stay whole runs of one sequence (else Vt is stored element
-    // by element: 58 against 42 us on the Latte-like spatial layer, 256-token
+    // V tiles must stay whole runs of one sequence (else Vt is not stored in
+    // whole chunks: 58 against 42 us with element stores on the Latte-like spatial layer, 256-token
     // sequences), which 128 x 192 keeps at 128 rows.
     const long slots = 2L * N_CUS;
     const long c128 = 2 * ((qkv_tiles(p, rm.n_rows, nw, 128, 128) + slots - 1) / slots);
@@ -214,8 +231,8 @@ hipError_t launch_proj_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a, h
     const float qscale = (float)(1.4426950408889634 / sqrt((double)p.dh));
     StageScope _stage(st, "proj_qkv");
     const int Lk = a.n_seq == 1 ? rm.n_rows : a.L;
-    // sequences of varying length: Vt slots per sequence, filled element by
-    // element; the attention masks their ends itself (no padding to zero)
+    // sequences of varying length: Vt slots per sequence, filled in quads of
+    // tokens; the attention masks their ends itself (no padding to zero)
     const bool varlen = a.seq_off != nullptr;
     // short sequences: V rows from the Q/K tiles (nw = 3), no V tiles
     const int nw = !varlen && attn_short(Lk) ? 3 : 2;
