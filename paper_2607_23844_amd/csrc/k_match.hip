@@ -141,8 +141,11 @@ hipError_t launch_inv_norm(const Plan &p, const void *x, float *inv, unsigned lo
 // squares of its ph rows of pw*C elements (16-byte chunks spread over the
 // block, wave partials added in a fixed order), stored at the tile's
 // top-left token; the blocks past the tiles clear pack and convert wo.
+// There are fewer tiles than compute units (64 of 147 KB on a Latte-like
+// layer), so a tile takes sixteen waves with four loads each in flight
+// (14.2 us with four waves and one load, 6.1 us this way).
 template <typename T>
-__global__ void k_tile_norm(const T *__restrict__ x, float *__restrict__ inv, int F, int N, int W, int k, int ph,
+__global__ __launch_bounds__(1024) void k_tile_norm(const T *__restrict__ x, float *__restrict__ inv, int F, int N, int W, int k, int ph,
                             int pw, int C, int norm_blocks, unsigned long long *__restrict__ pack, long n_pack,
                             const uint4 *__restrict__ wo, long n8, uint4 *__restrict__ wo16) {
     if ((int)blockIdx.x >= norm_blocks) {
@@ -154,26 +157,39 @@ __global__ void k_tile_norm(const T *__restrict__ x, float *__restrict__ inv, in
     for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n_pack; i += (long)norm_blocks * blockDim.x)
         pack[i] = 0ull;
     constexpr int VEC = 16 / sizeof(T);
-    __shared__ float wsum[4];
+    __shared__ float wsum[16];
     const int kk = k * k, f = blockIdx.x / kk, g = blockIdx.x - f * kk;
     const long tl = (long)f * N + (long)(g / k) * ph * W + (g % k) * pw;
-    const int cpr = pw * C / VEC;                  // chunks per tile row
+    const int cpr = pw * C / VEC, n_q = ph * cpr;   // 16-byte chunks per tile row and tile
     float ss = 0.f;
-    for (int q = threadIdx.x; q < ph * cpr; q += blockDim.x) {
-        const int row = q / cpr, c = (q - row * cpr) * VEC;
-        const uint4 v = *reinterpret_cast<const uint4 *>(x + (tl + (long)row * W) * C + c);
-        const T *e = reinterpret_cast<const T *>(&v);
+    for (int q0 = threadIdx.x; q0 < n_q; q0 += 4 * blockDim.x) {
+        // (a chunk past the end re-reads the last one, unbranched, and its
+        // sum is dropped)
+        uint4 v[4];
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) {
-            const float fv = Elem<T>::ld(e + j);
-            ss = fmaf(fv, fv, ss);
+        for (int u = 0; u < 4; ++u) {
+            const int q = min(q0 + u * (int)blockDim.x, n_q - 1);
+            const int row = q / cpr, c = (q - row * cpr) * VEC;
+            v[u] = *reinterpret_cast<const uint4 *>(x + (tl + (long)row * W) * C + c);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const T *e = reinterpret_cast<const T *>(&v[u]);
+            float part = ss;
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                const float fv = Elem<T>::ld(e + j);
+                part = fmaf(fv, fv, part);
+            }
+            ss = q0 + u * (int)blockDim.x < n_q ? part : ss;
         }
     }
     ss = wave_sum(ss);
     if ((threadIdx.x & (WAVE - 1)) == 0) wsum[threadIdx.x / WAVE] = ss;
     __syncthreads();
     if (threadIdx.x == 0) {
-        const float t = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+        float t = 0.f;
+        for (int w = 0; w < (int)(blockDim.x / WAVE); ++w) t += wsum[w];
         inv[tl] = t > 0.f ? (float)(1.0 / sqrt((double)t)) : 0.f;
     }
 }
@@ -183,12 +199,13 @@ hipError_t launch_tile_norm(const Plan &p, const void *x, float *inv, unsigned l
     StageScope _stage(st, "inv_norm");
     const int blocks = p.F * p.k * p.k;
     const long n8 = (wo && wo16 && p.bf16) ? n_wo / 8 : 0;
-    const int cvt_blocks = n8 > 0 ? (int)std::min<long>((n8 + 255) / 256, 1024) : 0;
+    const int threads = (long)p.ph * p.pw * p.C * p.esz >= 64 << 10 ? 1024 : 256;   // (four loads each over 64 KB)
+    const int cvt_blocks = n8 > 0 ? (int)std::min<long>((n8 + threads - 1) / threads, 1024) : 0;
     if (p.bf16)
-        launch_k(k_tile_norm<uint16_t>, blocks + cvt_blocks, 256, 0, st, (const uint16_t *)x, inv, p.F, p.N, p.W, p.k,
+        launch_k(k_tile_norm<uint16_t>, blocks + cvt_blocks, threads, 0, st, (const uint16_t *)x, inv, p.F, p.N, p.W, p.k,
                  p.ph, p.pw, p.C, blocks, node_pack, n_pack, (const uint4 *)wo, n8, (uint4 *)wo16);
     else
-        launch_k(k_tile_norm<float>, blocks, 256, 0, st, (const float *)x, inv, p.F, p.N, p.W, p.k, p.ph, p.pw, p.C,
+        launch_k(k_tile_norm<float>, blocks, threads, 0, st, (const float *)x, inv, p.F, p.N, p.W, p.k, p.ph, p.pw, p.C,
                  blocks, node_pack, n_pack, nullptr, 0, nullptr);
     return hipGetLastError();
 }
