@@ -1,5 +1,5 @@
 // Pieces shared by the GEMM-shaped kernels (projections, feed-forward):
-// XCD-grouped tile order, the LDS-staged row epilogue and the engine switch.
+// XCD-grouped tile order and the LDS-staged row epilogue (blocks of NT threads).
 #pragma once
 #include "oc_internal.h"
 #include "oc_launch.h"
@@ -45,25 +45,15 @@ __device__ __forceinline__ void stage_rows(const T &t, uint16_t *S, Cvt cvt, Col
 
 // Write the staged rows in 16-byte chunks: chunk (b, c0) (columns c0..c0+7,
 // c0 < ncol) goes to dst(b, c0); nullptr skips it.
-template <int BA, int BB, typename Dst>
+template <int BA, int BB, int NT = 256, typename Dst>
 __device__ __forceinline__ void write_rows(const uint16_t *S, int ncol, Dst dst) {
     constexpr int SROW = BA + 8, CPR = BA / 8;
-    for (int c = threadIdx.x; c < BB * CPR; c += 256) {
+    for (int c = threadIdx.x; c < BB * CPR; c += NT) {
         const int b = c / CPR, c0 = (c - b * CPR) * 8;
         if (c0 >= ncol) continue;
         uint16_t *d = dst(b, c0);
         if (d != nullptr) *reinterpret_cast<uint4 *>(d) = *reinterpret_cast<const uint4 *>(S + b * SROW + c0);
     }
-}
-
-struct RegRows { static constexpr bool dma = false; };
-struct DmaRows { static constexpr bool dma = true; };
-template <typename T, typename Rows>
-__device__ __forceinline__ void run_tile(T &t, uint16_t *lds, const uint16_t *const *rowsA,
-                                         const uint16_t *const *rowsB, const uint16_t *fbA, const uint16_t *fbB, int K,
-                                         Rows) {
-    if constexpr (Rows::dma) t.run(lds, rowsA, rowsB, fbA, fbB, K, 0, 0);
-    else t.run(lds, rowsA, rowsB, K, 0, 0);
 }
 
 template <typename KernelPtr>
