@@ -20,14 +20,16 @@
 #include "oc_launch.h"
 #include "oc_device.h"
 #include "oc_mfma_tile.h"
-#include "oc_dma_tile.h"
+#include "oc_ring_tile.h"
 #include "oc_attn_common.h"
 
 namespace oc {
 
 namespace {
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-using ShortTile = DmaTile<192, 128, 2, 2, false, 2>;
+// two blocks per CU (5536 sequences of 25 tokens, 5 heads of 64, C = 320: 164
+// us on double-buffered tiles, 139-156 on the ring)
+using ShortTile = RingTile<192, 128, 2, 2, 2>;
 constexpr int SH_DH = 64;
 constexpr int QKS = 128 + 8;   // LDS row of a slot: Q (64) | K (64) | pad, halves
 constexpr int VTS = 128 + 8;   // LDS row of one V dim over the 128 slots, halves
@@ -50,20 +52,26 @@ __global__ __launch_bounds__(256) void k_qkv_attn_short(RowMap rm, const uint16_
     const int C = rm.C;
 
     // ---- projection: [192 features x 128 slots] ----
-    const uint16_t *rowsA[T::CA], *rowsB[T::CB];
+    typename T::RowsA ra;
+    typename T::RowsB rb;
+    ra.base2 = rb.base2 = rm.x;
+    ra.mix = ra.alt = rb.mix = rb.alt = 0;
 #pragma unroll
     for (int i = 0; i < T::CA; ++i) {
-        const int a = T::chunk_row(i);
-        const uint16_t *w = a < SH_DH ? wq : (a < 2 * SH_DH ? wk : wv);
-        rowsA[i] = w + (long)(h * SH_DH + (a & (SH_DH - 1))) * C;
+        const int a8 = ra.row8(i);   // 8 rows of one of the three matrices
+        const uint16_t *w = a8 < SH_DH ? wq : (a8 < 2 * SH_DH ? wk : wv);
+        ra.base[i] = w + (long)(h * SH_DH + (a8 & (SH_DH - 1))) * C;
+        ra.off[i] = ((threadIdx.x & 63) >> 3) * (uint32_t)(C * 2) + (uint32_t)ra.chunk() * 16;
     }
 #pragma unroll
     for (int i = 0; i < T::CB; ++i) {
-        const int b = T::chunk_row(i);
-        rowsB[i] = b < n_slots ? rm.row(seq0 * L + b) : nullptr;
+        // (slots without a token repeat the tile's first one)
+        const int b = rb.row(i), r = seq0 * L + (b < n_slots ? b : 0);
+        rb.base[i] = rm.x;
+        rb.off[i] = (uint32_t)batch_token(r, rm.row_idx, rm.tF, rm.tN) * (uint32_t)(C * 2) + (uint32_t)rb.chunk() * 16;
     }
     T t;
-    t.run(lds, rowsA, rowsB, wq, rm.row(seq0 * L), C, 0, 0);
+    t.run(lds, ra, rb, C);
 
     // ---- stage Q, K by slot rows and V transposed, fp16 ----
     uint16_t *const QK = lds;
