@@ -7,6 +7,7 @@
 #include "oc_device.h"
 #include "oc_mfma_tile.h"
 #include "oc_dma_tile.h"
+#include "oc_ring_tile.h"
 #include "oc_f32_tile.h"
 #include "oc_attn_common.h"
 #include <algorithm>
@@ -221,7 +222,7 @@ hipError_t launch_tile_norm(const Plan &p, const void *x, float *inv, unsigned l
 // representative norm is applied before the arg-max, the candidate's own
 // norm (a positive constant per row) when unpacking.
 template <int BA, int BB, int WA, int WB, bool DMA>
-using MatchTile = typename std::conditional<DMA, DmaTile<BA, BB, WA, WB, false, 2>, MfmaTile<BA, BB, WA, WB>>::type;
+using MatchTile = typename std::conditional<DMA, DmaTile<BA, BB, WA, WB>, MfmaTile<BA, BB, WA, WB>>::type;
 
 template <int BA, int BB, int WA, int WB, bool DMA>
 __global__ __launch_bounds__(256) void k_match_mfma(const uint16_t *__restrict__ x, const float *__restrict__ inv,
@@ -302,47 +303,75 @@ __global__ __launch_bounds__(256) void k_match_mfma(const uint16_t *__restrict__
     }
 }
 
-// Sweep variant for many candidate tiles and several representative tiles:
-// block (candidate tile bt, group g) streams every representative tile (and
-// its candidates again, from L2) through one continuous double-buffered
-// LDS-DMA pipeline (small enough for two blocks per CU), keeps each
-// candidate's best (value, position) in registers and publishes it once (one
-// 64-bit atomic maximum per candidate).  The representative tiles of one
-// candidate tile are split over n_part consecutive blocks (adjacent logical
-// blocks run on one XCD at the same time, so they share the candidate rows
-// in its L2 instead of each block re-reading its own tile from memory for
-// every representative tile); their atomics merge the parts.  The group's
-// representative norms are staged in LDS first (D <= SWEEP_MAX_D).
-template <int BA, int BB, int WA, int WB>
-__global__ __launch_bounds__(256) void k_match_sweep(const uint16_t *__restrict__ x, const float *__restrict__ inv,
-                                                      GroupMap gm, int G, int S, int D, int K, int seg_len,
-                                                      long sub_stride, long item_stride, int n_bt, int n_at,
-                                                      int n_part, unsigned long long *__restrict__ node_pack) {
-    using T = DmaTile<BA, BB, WA, WB, false, 2>;
+// Token groups (descriptors of one contiguous run): ring-buffered tiles of
+// representatives (a) by candidates (b).  A block takes one candidate tile of
+// one group and n_at / n_part of its representative tiles, back to back in
+// one pipeline; it keeps each candidate's best (value, position) in registers
+// and merges it into node_pack once, by the packed atomic maximum.  The
+// block's representatives (offset and inverse norm) are tabled in LDS first.
+//
+// The grid holds the tiles that exist and no others: t_one candidate tiles
+// per patch of an unpaired unit, t_pair per patch of a frame pair, and a block
+// finds its group by counting through the units.  (A grid of the largest
+// group's tiles for every group, in contiguous ranges per XCD, left the XCDs
+// whose range held few pairs idle for much of the launch.)
+//
+// Bounded by the MFMA rate at the clock the load leaves (248 of 288 us with
+// the arg-max between the tiles reduced to a maximum).  Parts of one candidate
+// tile are adjacent, so they share its rows in one XCD's L2.  25 frames of 72
+// x 128 tokens of 320 channels, 5 pairs: 654 us on 128 x 128 tiles and the
+// full grid, 288 us this way; 12 pairs matched in 4 x 4 patches 91 -> 71;
+// 3072 x 1024 x 1536: 20.5 -> 19.8; 1024 tokens of C = 160 13.2 -> 8.4.
+template <int ID>
+__global__ __launch_bounds__(RING_THREADS<ID>) void k_match_ring(const uint16_t *__restrict__ x,
+                                                                 const float *__restrict__ inv, GroupMap gm,
+                                                                 int n_units, int S, int D, int K, int t_one,
+                                                                 int t_pair, int n_at, int n_part, int total,
+                                                                 unsigned long long *__restrict__ node_pack) {
+    using T = typename RingShape<ID, false>::Tile;
+    constexpr int BA = T::BA, BB = T::BB, NT = T::NT, WA = BA / T::WTA;
     extern __shared__ __align__(16) uint16_t lds[];
-    float *const snorm = reinterpret_cast<float *>(lds + T::LDS_BYTES / 2);   // n_at * BA norms after the ring
-    __shared__ float sv[WA * BB];
-    __shared__ int si[WA * BB];
-    const int lid = xcd_remap(blockIdx.x, n_bt * G * n_part);
-    const int part = lid % n_part, tl = lid / n_part;
-    const int bt = tl % n_bt, g = tl / n_bt;
+    float *const snorm = reinterpret_cast<float *>(lds + T::RING_BYTES / 2);
+    const int lid = xcd_remap(blockIdx.x, total);
+    const int part = lid % n_part, kk = gm.k * gm.k;
     const int u0 = part * n_at / n_part, u1 = (part + 1) * n_at / n_part;   // this block's representative tiles
-    const GroupMap::Grp gr = gm.group(g);
-    if (bt * BB >= gr.nsrc || u0 >= u1) return;
-    for (int a = threadIdx.x; a < n_at * BA; a += 256) {
-        const int id = a < D ? gm.dst_id(gr, a) : -1;
-        snorm[a] = id >= 0 ? inv[id] : -1.f;
+    uint32_t *const soff = reinterpret_cast<uint32_t *>(snorm + (u1 - u0) * BA);
+    int tl = lid / n_part, unit = 0, t_g = t_one;
+    if (gm.units == nullptr) {
+        unit = tl / (kk * t_one);
+        tl -= unit * kk * t_one;
+    } else {
+        int at = 0, first = 0;
+        unit = -1;
+        for (int u = 0; u < n_units; ++u) {
+            const int t_u = gm.group(u * kk).pair ? t_pair : t_one;
+            if (tl >= at && tl < at + kk * t_u) {
+                unit = u;
+                t_g = t_u;
+                first = at;
+            }
+            at += kk * t_u;
+        }
+        tl -= first;
+        if (unit < 0) return;   // (a unit table with fewer pairs than planned)
     }
-    __syncthreads();
-    const uint16_t *rowsB[T::CB];
+    const int g = unit * kk + tl / t_g, b0 = tl % t_g * BB;
+    const GroupMap::Grp gr = gm.group(g);
+    for (int a = threadIdx.x; a < (u1 - u0) * BA; a += NT) {
+        const int id = u0 * BA + a < D ? gm.dst_id(gr, u0 * BA + a) : -1;
+        snorm[a] = id >= 0 ? inv[id] : -1.f;                 // padding never wins
+        soff[a] = (uint32_t)max(id, 0) * (uint32_t)(K * 2);
+    }
+    typename T::RowsB rb;
+    rb.base2 = x;
+    rb.mix = rb.alt = 0;
 #pragma unroll
     for (int i = 0; i < T::CB; ++i) {
-        const int b = bt * BB + T::chunk_row(i);
-        const int id = b < S ? gm.src_id(gr, b) : -1;
-        rowsB[i] = id >= 0 ? x + (long)id * item_stride : nullptr;
+        const int b = b0 + rb.row(i), id = b < S ? gm.src_id(gr, b) : -1;
+        rb.base[i] = x;
+        rb.off[i] = (uint32_t)max(id, 0) * (uint32_t)(K * 2) + (uint32_t)rb.chunk() * 16;
     }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wa = wave / WB;
+    __syncthreads();
     float bv[T::TB];
     int bi[T::TB];
 #pragma unroll
@@ -351,68 +380,88 @@ __global__ __launch_bounds__(256) void k_match_sweep(const uint16_t *__restrict_
         bi[j] = -1;
     }
     T tile;
-    auto rows_a = [&](int u, int i) -> const uint16_t * {
-        const int a = (u0 + u) * BA + T::chunk_row(i);
-        const int id = a < D ? gm.dst_id(gr, a) : -1;
-        return id >= 0 ? x + (long)id * item_stride : nullptr;
+    auto load_a = [&](typename T::RowsA &ra, int u) {
+        ra.base2 = x;
+        ra.mix = ra.alt = 0;
+#pragma unroll
+        for (int i = 0; i < T::CA; ++i) {
+            ra.base[i] = x;
+            ra.off[i] = soff[u * BA + ra.row(i)] + (uint32_t)ra.chunk() * 16;
+        }
     };
-    // per tile: scale by the representative norms, take the tile maximum per
-    // candidate and lane half, and only when it beats the running best find
-    // its smallest position (tiles come in ascending position, so a later
-    // equal value never replaces an earlier one); the lane halves are merged
-    // once at the end
-    const int d_full = D - BA;   // tiles starting at or below this have only valid representatives
-    auto epi = [&](int ul) {
-        const int u = u0 + ul;
-        const bool full = u * BA <= d_full && gm.dst_id(gr, u * BA + BA - 1) >= 0;
+    // per tile: scale by the representative norms, take the maximum of 16
+    // accumulators (four quads of consecutive positions), and only when it
+    // beats the running best find its smallest position, the first quad that
+    // holds it and then the first in the quad (positions rise with the tiles,
+    // so a later equal value never replaces an earlier one); lane halves and
+    // waves are merged at the end
+    auto epi = [&](int u) {
+        const bool full = (u0 + u + 1) * BA <= D;
 #pragma unroll
-        for (int j = 0; j < T::TB; ++j)
+        for (int i = 0; i < T::TA; ++i) {
+            float w[16];
 #pragma unroll
-            for (int i = 0; i < T::TA; ++i) {
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const float4 v = *reinterpret_cast<const float4 *>(&snorm[u * BA + T::a_of(i, g4)]);
+                w[4 * g4] = v.x;
+                w[4 * g4 + 1] = v.y;
+                w[4 * g4 + 2] = v.z;
+                w[4 * g4 + 3] = v.w;
+            }
+            const int base = (u0 + u) * BA + T::a_of(i, 0);
+#pragma unroll
+            for (int j = 0; j < T::TB; ++j) {
                 float t[16];
 #pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                    const int al = u * BA + T::a_of(i, g4);
-                    const float4 w = *reinterpret_cast<const float4 *>(&snorm[al]);
-                    const float wv[4] = {w.x, w.y, w.z, w.w};
+                for (int k = 0; k < 16; ++k) t[k] = tile.acc[i][j][k] * w[k];
+                if (!full) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        float v = tile.acc[i][j][4 * g4 + e] * wv[e];
-                        if (!full && wv[e] < 0.f) v = -INFINITY;
-                        t[4 * g4 + e] = v;
-                    }
+                    for (int k = 0; k < 16; ++k)
+                        if (w[k] < 0.f) t[k] = -INFINITY;
                 }
-                float m = t[0];
+                float m4[4];
 #pragma unroll
-                for (int k = 1; k < 16; ++k) m = fmaxf(m, t[k]);
+                for (int q = 0; q < 4; ++q)
+                    m4[q] = fmaxf(fmaxf(fmaxf(t[4 * q], t[4 * q + 1]), t[4 * q + 2]), t[4 * q + 3]);
+                const float m = fmaxf(fmaxf(fmaxf(m4[0], m4[1]), m4[2]), m4[3]);
                 if (m > bv[j]) {
-                    int ix = -1;
+                    float s0 = t[12], s1 = t[13], s2 = t[14];
+                    int ix = base + 24;
 #pragma unroll
-                    for (int k = 15; k >= 0; --k)
-                        if (t[k] == m) ix = u * BA + T::a_of(i, k >> 2) + (k & 3);
+                    for (int q = 2; q >= 0; --q) {
+                        const bool here = m4[q] == m;
+                        s0 = here ? t[4 * q] : s0;
+                        s1 = here ? t[4 * q + 1] : s1;
+                        s2 = here ? t[4 * q + 2] : s2;
+                        ix = here ? base + 8 * q : ix;
+                    }
+                    ix += s0 == m ? 0 : s1 == m ? 1 : s2 == m ? 2 : 3;
                     bv[j] = m;
                     bi[j] = ix;
                 }
             }
+        }
     };
-    tile.run_tiles(lds, rows_a, rowsB, x, x, K, seg_len, sub_stride, u1 - u0, epi);
+    tile.run_tiles(lds, load_a, rb, K, u1 - u0, epi);
+    const int lane = threadIdx.x & 63, wa = (threadIdx.x >> 6) / (BB / T::WTB);
+    float *const sv = reinterpret_cast<float *>(lds);   // the ring, free now
+    int *const si = reinterpret_cast<int *>(sv + WA * BB);
 #pragma unroll
-    for (int j = 0; j < T::TB; ++j) argmax_merge(bv[j], bi[j], __shfl_xor(bv[j], 32, WAVE), __shfl_xor(bi[j], 32, WAVE));
-    if (lane < 32) {
-#pragma unroll
-        for (int j = 0; j < T::TB; ++j) {
-            const int bl = T::b_of(j);
-            sv[wa * BB + bl] = bv[j];
-            si[wa * BB + bl] = bi[j];
+    for (int j = 0; j < T::TB; ++j) {
+        argmax_merge(bv[j], bi[j], __shfl_xor(bv[j], 32, WAVE), __shfl_xor(bi[j], 32, WAVE));
+        if (lane < 32) {
+            sv[wa * BB + T::b_of(j)] = bv[j];
+            si[wa * BB + T::b_of(j)] = bi[j];
         }
     }
     __syncthreads();
-    for (int bl = threadIdx.x; bl < BB; bl += 256) {
+    for (int bl = threadIdx.x; bl < BB; bl += NT) {
         float v = sv[bl];
         int ix = si[bl];
+#pragma unroll
         for (int w = 1; w < WA; ++w) argmax_merge(v, ix, sv[w * BB + bl], si[w * BB + bl]);
-        const int b = bt * BB + bl;
-        if (b < S && ix >= 0) atomicMax(&node_pack[(long)g * S + b], pack_argmax(v, ix));
+        if (b0 + bl < gr.nsrc && b0 + bl < S && ix >= 0)
+            atomicMax(&node_pack[(long)g * S + b0 + bl], pack_argmax(v, ix));
     }
 }
 
@@ -619,25 +668,54 @@ static hipError_t go_match(const Plan &p, const uint16_t *x, const float *inv, c
     return hipGetLastError();
 }
 
-template <int BA, int BB, int WA, int WB>
-static hipError_t go_sweep(const Plan &p, const uint16_t *x, const float *inv, const GroupMap &gm, int K,
-                           int seg_len, long sub_stride, long item_stride, unsigned long long *node_pack,
-                           hipStream_t st) {
-    using T = DmaTile<BA, BB, WA, WB, false, 2>;
-    const int G = p.n_groups, S = p.n_src_max, D = p.n_dst_max;
-    const int n_bt = cdiv(S, BB), n_at = cdiv(D, BA);
-    if (n_at * BA > SWEEP_MAX_D) return hipErrorInvalidValue;
-    const size_t lds = T::LDS_BYTES + (size_t)n_at * BA * 4;
-    hipError_t e = allow_lds(k_match_sweep<BA, BB, WA, WB>, lds);
-    if (e != hipSuccess) return e;
-    // two blocks per candidate tile once each keeps three or more
-    // representative tiles (SVD-XT-like frames: 8x less memory traffic than
-    // one block, 203 against 1627 MiB per launch, at the same time; three or
-    // six parts measured no faster)
-    const int n_part = n_at >= 6 ? 2 : 1;
-    launch_k(k_match_sweep<BA, BB, WA, WB>, n_bt * G * n_part, 256, lds, st, x, inv, gm, G, S, D, K, seg_len,
-             sub_stride, item_stride, n_bt, n_at, n_part, node_pack);
-    return hipGetLastError();
+// Tile shape and parts per candidate tile with the lowest cost: each block
+// pays a shape's fixed part once and, per representative tile, its steps and
+// the arg-max (2.7e-5 us per product on its own unit: three to four vector
+// instructions each).
+constexpr size_t MATCH_LDS = 160 * 1024;   // of a compute unit
+struct MatchPick { int id, n_part; };
+static MatchPick match_pick(const Plan &p, int n_pairs) {
+    const int kk = p.k * p.k, D = p.n_dst_max, nk = cdiv(p.C, 64);
+    constexpr size_t ring[N_RING_SHAPES] = {RING_LDS<0>, RING_LDS<1>, RING_LDS<2>, RING_LDS<3>, RING_LDS<4>,
+                                            RING_LDS<5>, RING_LDS<6>, RING_LDS<7>, RING_LDS<8>, RING_LDS<9>};
+    MatchPick best{-1, 1};
+    float best_t = 0.f;
+    for (int i = 0; i < N_RING_SHAPES; ++i) {
+        const RingShapeCost &c = RING_SHAPES[i];
+        const int n_at = cdiv(D, c.BA);
+        const long bts = (long)kk * ((long)(p.n_units - n_pairs) * cdiv(p.np_src, c.BB) +
+                                     (long)n_pairs * cdiv(p.np + p.np_src, c.BB));
+        for (int parts = 1; parts <= n_at; ++parts) {
+            const int per = cdiv(n_at, parts);   // representative tiles of the longest block
+            if (parts > 1 && per == cdiv(n_at, parts - 1)) continue;
+            if ((ring[i] + (size_t)per * c.BA * 8) * c.resident > MATCH_LDS) continue;
+            const float t = ring_cost(c, nk * per, bts * parts, 2.7e-5f * c.BA * c.BB * per);
+            if (best.id < 0 || t < best_t) {
+                best = MatchPick{i, parts};
+                best_t = t;
+            }
+        }
+    }
+    return best;
+}
+
+static hipError_t go_ring(const Plan &p, const uint16_t *x, const float *inv, const GroupMap &gm,
+                          unsigned long long *node_pack, hipStream_t st) {
+    const int n_pairs = gm.units != nullptr ? p.R_f : 0, kk = p.k * p.k;
+    const MatchPick pick = match_pick(p, n_pairs);
+    return ring_dispatch(pick.id, [&](auto c) -> hipError_t {
+        constexpr int ID = decltype(c)::value;
+        using T = typename RingShape<ID, false>::Tile;
+        const int n_at = cdiv(p.n_dst_max, T::BA);
+        const int t_one = cdiv(p.np_src, T::BB), t_pair = cdiv(p.np + p.np_src, T::BB);
+        const int total = kk * ((p.n_units - n_pairs) * t_one + n_pairs * t_pair) * pick.n_part;
+        const size_t lds = T::RING_BYTES + (size_t)cdiv(n_at, pick.n_part) * T::BA * 8;
+        const hipError_t e = raise_lds_limit((const void *)k_match_ring<ID>, MATCH_LDS);
+        if (e != hipSuccess) return e;
+        launch_k(k_match_ring<ID>, total, T::NT, lds, st, x, inv, gm, p.n_units, p.n_src_max, p.n_dst_max, p.C, t_one,
+                 t_pair, n_at, pick.n_part, total, node_pack);
+        return hipGetLastError();
+    });
 }
 
 template <int BA, int BB, int WA, int WB, bool DMA>
@@ -691,10 +769,8 @@ hipError_t launch_match(const Plan &p, const void *x, const float *inv, const in
                 // long descriptors, few tiles: split K (64-row tiles)
                 e = go_split<64, 64, 2, 2, true>(p, ms, xb, inv, gm, seg_len, sub_stride, item_stride, part,
                                                  node_pack, st);
-            } else if (D > 64 && dma && match_sweeps(p)) {
-                // many candidate tiles: each block sweeps all representative tiles
-                e = go_sweep<128, 128, 2, 2>(p, xb, inv, gm, K, seg_len, sub_stride, item_stride, node_pack,
-                                                   st);
+            } else if (p.kind == KIND_TOKEN) {
+                e = go_ring(p, xb, inv, gm, node_pack, st);
             } else if (D > 64 && dma && (long)cdiv(D, 128) * cdiv(S, 64) * G < 2L * N_CUS) {
                 // a 128 x 64 grid under two blocks per CU: 64 x 64 tiles, three
                 // to five per CU (the SD3-like layer: 768 blocks, 20 against 23 us)

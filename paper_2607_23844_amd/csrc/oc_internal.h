@@ -83,8 +83,8 @@ hipError_t launch_inv_norm(const Plan &p, const void *x, float *inv, unsigned lo
 // Similarity kernel choice (bf16): long descriptors over few 64x64 tiles
 // (Block Cache) split K into n_split ranges of kc elements, each inside one
 // segment of the descriptor, with fp32 partials [n_split][G][S][D] in the
-// workspace; many candidate tiles with several representative tiles sweep
-// the representatives per candidate tile; otherwise one block per tile pair.
+// workspace; token groups run on ring-buffered tiles that sweep the
+// representatives; otherwise one block per tile pair.
 struct MatchSplit { int n_split, kc; };
 // Descriptor geometry of the matched items: item id i starts at element
 // i * item_stride of x and is K elements long, read as segments of seg_len
@@ -118,12 +118,6 @@ inline MatchSplit match_split(const Plan &p) {
     m.n_split = nk / sps;
     m.kc = sps * 64;
     return m;
-}
-constexpr int SWEEP_MAX_D = 4096;   // representatives per group for the sweep variant (norms in LDS)
-inline bool match_sweeps(const Plan &p) {
-    const int n_bt = (p.n_src_max + 127) / 128, n_at = (p.n_dst_max + 127) / 128;
-    return p.bf16 && p.kind == KIND_TOKEN && p.C % 64 == 0 && n_at >= 2 && n_at * 128 <= SWEEP_MAX_D &&
-           (long)n_bt * p.n_groups >= 512;
 }
 // node_max == nullptr: node_pack only (the selection unpacks it); part: the
 // split-K partials (match_split), unused otherwise

@@ -164,6 +164,101 @@ struct RingTile {
         __syncthreads();   // the epilogue may reuse the ring
     }
 
+    // Several tiles along A against the same B rows, back to back in one
+    // pipeline (the ring is not drained between tiles): load_a(rows, u) fills
+    // the rows of tile u, and after tile u's last step epi(u) consumes acc.
+    // Neither may touch the ring or leave global loads in flight (the waits
+    // below count the ring's loads only).
+    template <typename LoadA, typename Epi>
+    __device__ __forceinline__ void run_tiles(uint16_t *lds, LoadA load_a, const RowsB &rb, int K, int n_tiles,
+                                              Epi epi) {
+        const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+        const int wa = wave / WB, wb = wave % WB, lr = lane & 31, lh = lane >> 5;
+        const int nk = (K + BK - 1) / BK, ns = nk * n_tiles;
+        const uint32_t tail = (nk - 1) * BK + RowsA::chunk() * 8 < K ? 0u : RING_RECORDS;
+        RowsA ra;
+        load_a(ra, 0);
+        int iu = 0, ik = 0;   // tile and step of the next loads
+        auto issue = [&](int d, uint16_t *st, uint32_t oob) {
+            if (d < CA) dma(ra, d, st + (wave + NW * d) * 512, ik * BK * 2, oob);
+            else dma(rb, d - CA, st + BA * BK + (wave + NW * (d - CA)) * 512, ik * BK * 2, oob);
+        };
+        auto advance = [&]() {
+            if (++ik == nk) {
+                ik = 0;
+                if (++iu < n_tiles) load_a(ra, iu);
+            }
+        };
+        int oa[4], ob[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int c = ((ks * 2 + lh) ^ ((lr >> 1) & 7)) << 3;
+            oa[ks] = (wa * WTA + lr) * BK + c;
+            ob[ks] = BA * BK + (wb * WTB + lr) * BK + c;
+        }
+        frag fa[2][TA], fb[2][TB];
+        constexpr int NR = TA + TB, NM = TA * TB;
+        auto read = [&](int r, const uint16_t *st, int ks, int s) {
+            if (r == 0) fa[s][0] = *reinterpret_cast<const frag *>(st + oa[ks]);
+            else if (r <= TB) fb[s][r - 1] = *reinterpret_cast<const frag *>(st + ob[ks] + (r - 1) * 32 * BK);
+            else if (r < NR) fa[s][r - TB] = *reinterpret_cast<const frag *>(st + oa[ks] + (r - TB) * 32 * BK);
+        };
+        // as in run(); fresh: the tile's first products (the accumulators start at zero)
+        auto phase = [&](auto fresh, int s, const uint16_t *nst, int nks, uint16_t *dst, bool go, uint32_t oob) {
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+#pragma unroll
+                for (int r = m * NR / NM; r < (m + 1) * NR / NM; ++r) read(r, nst, nks, s ^ 1);
+                f32x16 &c = acc[m / TB][m % TB];
+                c = mma(fa[s][m / TB], fb[s][m % TB], decltype(fresh)::value ? f32x16{} : c);
+                if (dst != nullptr && go) {
+#pragma unroll
+                    for (int d = m * IPT / NM; d < (m + 1) * IPT / NM; ++d) issue(d, dst, oob);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+#pragma unroll
+        for (int q = 0; q < NST; ++q)
+            if (q < ns) {
+#pragma unroll
+                for (int d = 0; d < IPT; ++d) issue(d, lds + q * STAGE, ik + 1 < nk ? 0u : tail);
+                advance();
+            }
+        if (ns >= NST) {
+            OC_WAIT_VMCNT((NST - 1) * IPT);
+        } else {
+            OC_WAIT_VMCNT(0);
+        }
+        barrier_lds();
+#pragma unroll
+        for (int r = 0; r < NR; ++r) read(r, lds, 0, 0);
+        uint16_t *st = lds;
+        int kt = 0, u = 0;
+        for (int s = 0; s < ns; ++s) {
+            uint16_t *const ot = st + STAGE == lds + NST * STAGE ? lds : st + STAGE;
+            if (kt == 0) phase(std::true_type{}, 0, st, 1, nullptr, false, 0);
+            else phase(std::false_type{}, 0, st, 1, nullptr, false, 0);
+            phase(std::false_type{}, 1, st, 2, nullptr, false, 0);
+            phase(std::false_type{}, 0, st, 3, nullptr, false, 0);
+            if (s + NST - 1 < ns) {
+                OC_WAIT_VMCNT((NST - 2) * IPT);
+            } else {
+                OC_WAIT_VMCNT(0);
+            }
+            barrier_lds();
+            phase(std::false_type{}, 1, ot, 0, st, s + NST < ns, ik + 1 < nk ? 0u : tail);
+            if (s + NST < ns) advance();
+            st = ot;
+            if (++kt == nk) {
+                epi(u);
+                kt = 0;
+                ++u;
+            }
+        }
+        __syncthreads();   // the caller may reuse the ring
+    }
+
     __device__ __forceinline__ static int a_of(int i, int g) {
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         return (wave / WB) * WTA + i * 32 + 8 * g + 4 * (lane >> 5);
@@ -232,6 +327,16 @@ template <bool F16> struct RingShape<7, F16> { using Tile = RingTile<160, 128, 1
 template <bool F16> struct RingShape<8, F16> { using Tile = RingTile<64, 64, 2, 2, 3, F16>; };
 template <bool F16> struct RingShape<9, F16> { using Tile = RingTile<128, 64, 2, 2, 3, F16>; };
 template <int ID> constexpr int RING_THREADS = RingShape<ID, false>::Tile::NT;
+template <int ID> constexpr size_t RING_LDS = RingShape<ID, false>::Tile::RING_BYTES;
+
+// us for `blocks` blocks of nk steps each, with `epi` us of other work per block
+inline float ring_cost(const RingShapeCost &c, int nk, long blocks, float epi = 0.f) {
+    const long units = (blocks + 255) / 256, full = units / c.resident;
+    const int rest = (int)(units % c.resident);
+    float t = (float)full * (c.fixed + nk * c.step[c.resident - 1] + epi * c.resident);
+    if (rest > 0) t += c.fixed + nk * c.step[rest - 1] + epi * rest;
+    return t;
+}
 
 // The shape with the lowest cost for K elements; tiles(BA, BB): tiles of the launch.
 template <typename Tiles>
@@ -240,11 +345,7 @@ inline int ring_pick(int K, Tiles tiles) {
     int best = 0;
     float best_t = 0.f;
     for (int i = 0; i < N_RING_SHAPES; ++i) {
-        const RingShapeCost &c = RING_SHAPES[i];
-        const long units = (tiles(c.BA, c.BB) + 255) / 256, full = units / c.resident;
-        const int rest = (int)(units % c.resident);
-        float t = (float)full * (c.fixed + nk * c.step[c.resident - 1]);
-        if (rest > 0) t += c.fixed + nk * c.step[rest - 1];
+        const float t = ring_cost(RING_SHAPES[i], nk, tiles(RING_SHAPES[i].BA, RING_SHAPES[i].BB));
         if (i == 0 || t < best_t) {
             best = i;
             best_t = t;
