@@ -317,10 +317,12 @@ hipError_t launch_attention(const Plan &p, const AttnArgs &a, hipStream_t st) {
             if ((e = launch_qkv_attn_short(p, rm, a, st)) != hipSuccess) return e;
             return launch_proj_out(p, n_rows, a, st);
         }
-        e = launch_proj_qkv(p, rm, a, st);
+        e = launch_proj_qkv(p, rm, a, st);   // (converts wo when no earlier launch has)
         if (e != hipSuccess) return e;
         if ((e = launch_flash(p, a, Lk, st)) != hipSuccess) return e;
-        return launch_proj_out(p, n_rows, a, st);
+        AttnArgs o = a;
+        o.wo16_ready = 1;
+        return launch_proj_out(p, n_rows, o, st);
     }
     const RowMapF rm{(const float *)a.x, a.row_idx, a.n_main, (const float *)a.ctx, n_rows, p.C, a.tF, a.tN};
     hipError_t e;

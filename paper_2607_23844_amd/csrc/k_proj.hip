@@ -33,6 +33,7 @@
 #include "oc_attn_common.h"
 #include "oc_gemm_epi.h"
 #include "oc_ring_tile.h"
+#include <algorithm>
 
 namespace oc {
 
@@ -65,6 +66,20 @@ __device__ __forceinline__ void ring_batch_rows(RingRows<N, NW> &w, const RowMap
     }
 }
 
+// bf16 -> fp16 (exact in the fp16 normal range, saturating outside), chunks i,
+// i + step, ... of 8 elements, four loads in flight
+__device__ __forceinline__ void to_f16(const uint4 *__restrict__ src, long n8, uint4 *__restrict__ dst, long i,
+                                       long step) {
+    for (; i < n8; i += 4 * step) {
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = src[min(i + u * step, n8 - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + u * step < n8) dst[i + u * step] = bf16x8_to_f16x8(v[u]);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Q, K and V in one launch.  The first n_qk tiles are row tiles: a in [0,
 // nw*hd) are rows of wq, wk (and wv when nw = 3), b = batch rows, staged as
@@ -75,18 +90,25 @@ __device__ __forceinline__ void ring_batch_rows(RingRows<N, NW> &w, const RowMap
 // sequence (a single sequence, or L a multiple of the tile) are written as Vt
 // rows: the positions of the tile's tokens, zero for positions past the end
 // (the key padding up to lpad), in whole chunks.  Otherwise they are stored in
-// quads of tokens and the key padding is zeroed separately.
+// quads of tokens and the key padding is zeroed separately.  The blocks past
+// the tiles convert wo for the output projection where no earlier launch of
+// the call has (the uncached layer and the attention entry point: a launch of
+// its own took 4.5 us of 263 on the SD3-like layer, 4.4 of 220 by stages).
 // ---------------------------------------------------------------------------
 template <int ID>
 __global__ __launch_bounds__(RING_THREADS<ID>) void k_proj_qkv(
     RowMap rm, const uint16_t *__restrict__ wq, const uint16_t *__restrict__ wk, const uint16_t *__restrict__ wv,
     int hd, int dh, float qscale, int nw, int n_qk_at, int n_bt, int n_v_at, int n_v_bt, int n_seq, int L, int lpad,
     const int32_t *__restrict__ seq_off, uint16_t *__restrict__ Q, uint16_t *__restrict__ K,
-    uint16_t *__restrict__ Vt) {
+    uint16_t *__restrict__ Vt, const uint4 *__restrict__ wo, long n8, uint4 *__restrict__ wo16) {
     using T = typename RingShape<ID, false>::Tile;
     constexpr int BA = T::BA, BB = T::BB, NT = T::NT;
     extern __shared__ __align__(16) uint16_t lds[];
     const int n_qk = n_qk_at * n_bt, total = n_qk + n_v_at * n_v_bt;
+    if ((int)blockIdx.x >= total) {
+        to_f16(wo, n8, wo16, (long)(blockIdx.x - total) * NT + threadIdx.x, (long)(gridDim.x - total) * NT);
+        return;
+    }
     const int lid = xcd_remap(blockIdx.x, total);
     typename T::RowsA ra;
     typename T::RowsB rb;
@@ -187,6 +209,7 @@ hipError_t launch_proj_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a, h
     // short sequences: V rows from the Q/K tiles (nw = 3), no V tiles
     const int nw = a.seq_off == nullptr && attn_short(Lk) ? 3 : 2;
     const auto v_at = [&](int BA) { return nw == 3 ? 0 : cdiv(rm.n_rows, BA); };
+    const long n8 = a.wo16_ready ? 0 : (long)p.C * p.hd / 8;
     const int id = ring_pick(p.C, [&](int BA, int BB) {
         return (long)cdiv(nw * p.hd, BA) * cdiv(rm.n_rows, BB) + (long)v_at(BA) * cdiv(p.hd, BB);
     });
@@ -197,10 +220,11 @@ hipError_t launch_proj_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a, h
         if (e != hipSuccess) return e;
         const int n_qk_at = cdiv(nw * p.hd, T::BA), n_bt = cdiv(rm.n_rows, T::BB);
         const int n_v_at = v_at(T::BA), n_v_bt = nw == 3 ? 0 : cdiv(p.hd, T::BB);
-        launch_k(k_proj_qkv<ID>, n_qk_at * n_bt + n_v_at * n_v_bt, T::NT, T::LDS_BYTES, st, rm,
+        const int cvt_blocks = (int)std::min<long>((n8 + 4 * T::NT - 1) / (4 * T::NT), N_CUS);
+        launch_k(k_proj_qkv<ID>, n_qk_at * n_bt + n_v_at * n_v_bt + cvt_blocks, T::NT, T::LDS_BYTES, st, rm,
                  (const uint16_t *)a.wq, (const uint16_t *)a.wk, (const uint16_t *)a.wv, p.hd, p.dh, qscale, nw,
                  n_qk_at, n_bt, n_v_at, n_v_bt, a.n_seq, a.L, a.lpad, a.seq_off, (uint16_t *)a.q, (uint16_t *)a.k,
-                 (uint16_t *)a.vt);
+                 (uint16_t *)a.vt, (const uint4 *)a.wo, n8, (uint4 *)a.wo16);
         return hipGetLastError();
     });
 }
@@ -236,10 +260,8 @@ __global__ __launch_bounds__(RING_THREADS<ID>) void k_proj_out(
     });
 }
 
-// bf16 -> fp16 (exact in the fp16 normal range, saturating outside), 8 per thread
 __global__ void k_to_f16(const uint4 *__restrict__ src, long n8, uint4 *__restrict__ dst) {
-    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n8; i += (long)gridDim.x * blockDim.x)
-        dst[i] = bf16x8_to_f16x8(src[i]);
+    to_f16(src, n8, dst, (long)blockIdx.x * blockDim.x + threadIdx.x, (long)gridDim.x * blockDim.x);
 }
 
 hipError_t launch_proj_out(const Plan &p, int n_rows, const AttnArgs &a, hipStream_t st) {
