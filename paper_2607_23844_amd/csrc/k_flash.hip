@@ -273,6 +273,20 @@ __global__ __launch_bounds__(NW * 64) void k_flash(const uint16_t *__restrict__ 
     // -m in every slot: the first S MFMA of a tile adds it (changes only on the slow path)
     f32x16 negm = f32x16{};
 
+    // The two waves that share a SIMD otherwise run their MFMA and softmax
+    // phases against each other; a standing difference of priority lets one
+    // take each unit at once and the other fill what is left.  Eight-wave
+    // blocks: one half of the waves (SD3-like r = 0.5, 47.9 -> 46.7 us).
+    // Four-wave blocks, two per compute unit: every second round of 256
+    // blocks, counted so that the last, which ends the launch, is among them
+    // (SD3-like uncached 169-172 -> 163-166, r = 0.25 104.3 -> 101.7, 20
+    // sequences of 4608 keys 644 -> 632, 13 of them 430 -> 421; with the
+    // other rounds preferred 172, 104.5, 651 and 437).
+    if constexpr (DMA && NW == 8) {
+        if (wv >= 4) __builtin_amdgcn_s_setprio(3);
+    } else if constexpr (DMA) {
+        if (((((int)gridDim.x - 1) >> 8) - ((int)blockIdx.x >> 8)) % 2 == 0) __builtin_amdgcn_s_setprio(2);
+    }
     const int n_kt = cdiv(Lk, KT);
     constexpr int IPT = IK + IV;   // DMA instructions per wave and tile
     if constexpr (DMA) {
