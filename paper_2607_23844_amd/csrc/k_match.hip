@@ -303,7 +303,8 @@ __global__ __launch_bounds__(256) void k_match_mfma(const uint16_t *__restrict__
     }
 }
 
-// Token groups (descriptors of one contiguous run): ring-buffered tiles of
+// Token groups, and blocks whose channels are whole K steps (a position's
+// descriptor is a segment per frame): ring-buffered tiles of
 // representatives (a) by candidates (b).  A block takes one candidate tile of
 // one group and n_at / n_part of its representative tiles, back to back in
 // one pipeline; it keeps each candidate's best (value, position) in registers
@@ -321,11 +322,13 @@ __global__ __launch_bounds__(256) void k_match_mfma(const uint16_t *__restrict__
 // tile are adjacent, so they share its rows in one XCD's L2.  25 frames of 72
 // x 128 tokens of 320 channels, 5 pairs: 654 us on 128 x 128 tiles and the
 // full grid, 288 us this way; 12 pairs matched in 4 x 4 patches 91 -> 71;
-// 3072 x 1024 x 1536: 20.5 -> 19.8; 1024 tokens of C = 160 13.2 -> 8.4.
+// 3072 x 1024 x 1536: 20.5 -> 19.8; 1024 tokens of C = 160 13.2 -> 8.4; blocks
+// of 25 frames of 320 channels, 16 groups of 432 x 144: 78 -> 62.
 template <int ID>
 __global__ __launch_bounds__(RING_THREADS<ID>) void k_match_ring(const uint16_t *__restrict__ x,
                                                                  const float *__restrict__ inv, GroupMap gm,
-                                                                 int n_units, int S, int D, int K, int t_one,
+                                                                 int n_units, int S, int D, int K, int seg_len,
+                                                                 long sub_stride, long item_stride, int t_one,
                                                                  int t_pair, int n_at, int n_part, int total,
                                                                  unsigned long long *__restrict__ node_pack) {
     using T = typename RingShape<ID, false>::Tile;
@@ -360,7 +363,7 @@ __global__ __launch_bounds__(RING_THREADS<ID>) void k_match_ring(const uint16_t 
     for (int a = threadIdx.x; a < (u1 - u0) * BA; a += NT) {
         const int id = u0 * BA + a < D ? gm.dst_id(gr, u0 * BA + a) : -1;
         snorm[a] = id >= 0 ? inv[id] : -1.f;                 // padding never wins
-        soff[a] = (uint32_t)max(id, 0) * (uint32_t)(K * 2);
+        soff[a] = (uint32_t)max(id, 0) * (uint32_t)(item_stride * 2);
     }
     typename T::RowsB rb;
     rb.base2 = x;
@@ -369,7 +372,7 @@ __global__ __launch_bounds__(RING_THREADS<ID>) void k_match_ring(const uint16_t 
     for (int i = 0; i < T::CB; ++i) {
         const int b = b0 + rb.row(i), id = b < S ? gm.src_id(gr, b) : -1;
         rb.base[i] = x;
-        rb.off[i] = (uint32_t)max(id, 0) * (uint32_t)(K * 2) + (uint32_t)rb.chunk() * 16;
+        rb.off[i] = (uint32_t)max(id, 0) * (uint32_t)(item_stride * 2) + (uint32_t)rb.chunk() * 16;
     }
     __syncthreads();
     float bv[T::TB];
@@ -442,7 +445,7 @@ __global__ __launch_bounds__(RING_THREADS<ID>) void k_match_ring(const uint16_t 
             }
         }
     };
-    tile.run_tiles(lds, load_a, rb, K, u1 - u0, epi);
+    tile.run_tiles(lds, load_a, rb, K, seg_len, sub_stride, u1 - u0, epi);
     const int lane = threadIdx.x & 63, wa = (threadIdx.x >> 6) / (BB / T::WTB);
     float *const sv = reinterpret_cast<float *>(lds);   // the ring, free now
     int *const si = reinterpret_cast<int *>(sv + WA * BB);
@@ -674,8 +677,8 @@ static hipError_t go_match(const Plan &p, const uint16_t *x, const float *inv, c
 // instructions each).
 constexpr size_t MATCH_LDS = 160 * 1024;   // of a compute unit
 struct MatchPick { int id, n_part; };
-static MatchPick match_pick(const Plan &p, int n_pairs) {
-    const int kk = p.k * p.k, D = p.n_dst_max, nk = cdiv(p.C, 64);
+static MatchPick match_pick(const Plan &p, int K, int n_units, int n_pairs) {
+    const int kk = p.k * p.k, D = p.n_dst_max, nk = cdiv(K, 64);
     constexpr size_t ring[N_RING_SHAPES] = {RING_LDS<0>, RING_LDS<1>, RING_LDS<2>, RING_LDS<3>, RING_LDS<4>,
                                             RING_LDS<5>, RING_LDS<6>, RING_LDS<7>, RING_LDS<8>, RING_LDS<9>};
     MatchPick best{-1, 1};
@@ -683,7 +686,7 @@ static MatchPick match_pick(const Plan &p, int n_pairs) {
     for (int i = 0; i < N_RING_SHAPES; ++i) {
         const RingShapeCost &c = RING_SHAPES[i];
         const int n_at = cdiv(D, c.BA);
-        const long bts = (long)kk * ((long)(p.n_units - n_pairs) * cdiv(p.np_src, c.BB) +
+        const long bts = (long)kk * ((long)(n_units - n_pairs) * cdiv(p.np_src, c.BB) +
                                      (long)n_pairs * cdiv(p.np + p.np_src, c.BB));
         for (int parts = 1; parts <= n_at; ++parts) {
             const int per = cdiv(n_at, parts);   // representative tiles of the longest block
@@ -699,21 +702,22 @@ static MatchPick match_pick(const Plan &p, int n_pairs) {
     return best;
 }
 
-static hipError_t go_ring(const Plan &p, const uint16_t *x, const float *inv, const GroupMap &gm,
+static hipError_t go_ring(const Plan &p, const uint16_t *x, const float *inv, const GroupMap &gm, const MatchGeom &mg,
                           unsigned long long *node_pack, hipStream_t st) {
     const int n_pairs = gm.units != nullptr ? p.R_f : 0, kk = p.k * p.k;
-    const MatchPick pick = match_pick(p, n_pairs);
+    const int n_units = p.kind == KIND_BLOCK ? 1 : p.n_units;   // (blocks: one group per patch)
+    const MatchPick pick = match_pick(p, mg.K, n_units, n_pairs);
     return ring_dispatch(pick.id, [&](auto c) -> hipError_t {
         constexpr int ID = decltype(c)::value;
         using T = typename RingShape<ID, false>::Tile;
         const int n_at = cdiv(p.n_dst_max, T::BA);
         const int t_one = cdiv(p.np_src, T::BB), t_pair = cdiv(p.np + p.np_src, T::BB);
-        const int total = kk * ((p.n_units - n_pairs) * t_one + n_pairs * t_pair) * pick.n_part;
+        const int total = kk * ((n_units - n_pairs) * t_one + n_pairs * t_pair) * pick.n_part;
         const size_t lds = T::RING_BYTES + (size_t)cdiv(n_at, pick.n_part) * T::BA * 8;
         const hipError_t e = raise_lds_limit((const void *)k_match_ring<ID>, MATCH_LDS);
         if (e != hipSuccess) return e;
-        launch_k(k_match_ring<ID>, total, T::NT, lds, st, x, inv, gm, p.n_units, p.n_src_max, p.n_dst_max, p.C, t_one,
-                 t_pair, n_at, pick.n_part, total, node_pack);
+        launch_k(k_match_ring<ID>, total, T::NT, lds, st, x, inv, gm, n_units, p.n_src_max, p.n_dst_max, mg.K,
+                 mg.seg_len, mg.sub_stride, mg.item_stride, t_one, t_pair, n_at, pick.n_part, total, node_pack);
         return hipGetLastError();
     });
 }
@@ -769,8 +773,8 @@ hipError_t launch_match(const Plan &p, const void *x, const float *inv, const in
                 // long descriptors, few tiles: split K (64-row tiles)
                 e = go_split<64, 64, 2, 2, true>(p, ms, xb, inv, gm, seg_len, sub_stride, item_stride, part,
                                                  node_pack, st);
-            } else if (p.kind == KIND_TOKEN) {
-                e = go_ring(p, xb, inv, gm, node_pack, st);
+            } else if (p.kind == KIND_TOKEN || (p.kind == KIND_BLOCK && dma)) {
+                e = go_ring(p, xb, inv, gm, mg, node_pack, st);
             } else if (D > 64 && dma && (long)cdiv(D, 128) * cdiv(S, 64) * G < 2L * N_CUS) {
                 // a 128 x 64 grid under two blocks per CU: 64 x 64 tiles, three
                 // to five per CU (the SD3-like layer: 768 blocks, 20 against 23 us)

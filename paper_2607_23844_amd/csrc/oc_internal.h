@@ -83,8 +83,9 @@ hipError_t launch_inv_norm(const Plan &p, const void *x, float *inv, unsigned lo
 // Similarity kernel choice (bf16): long descriptors over few 64x64 tiles
 // (Block Cache) split K into n_split ranges of kc elements, each inside one
 // segment of the descriptor, with fp32 partials [n_split][G][S][D] in the
-// workspace; token groups run on ring-buffered tiles that sweep the
-// representatives; otherwise one block per tile pair.
+// workspace; other token and block groups run on ring-buffered tiles that
+// sweep the representatives; what is left (frame tiles, blocks whose channels
+// are no whole K steps) takes one block per tile pair.
 struct MatchSplit { int n_split, kc; };
 // Descriptor geometry of the matched items: item id i starts at element
 // i * item_stride of x and is K elements long, read as segments of seg_len

@@ -168,26 +168,37 @@ struct RingTile {
     // pipeline (the ring is not drained between tiles): load_a(rows, u) fills
     // the rows of tile u, and after tile u's last step epi(u) consumes acc.
     // Neither may touch the ring or leave global loads in flight (the waits
-    // below count the ring's loads only).
+    // below count the ring's loads only).  seg_len > 0 (a multiple of 64 that
+    // divides K): a row is K / seg_len segments, sub_stride elements apart.
     template <typename LoadA, typename Epi>
-    __device__ __forceinline__ void run_tiles(uint16_t *lds, LoadA load_a, const RowsB &rb, int K, int n_tiles,
-                                              Epi epi) {
+    __device__ __forceinline__ void run_tiles(uint16_t *lds, LoadA load_a, RowsB rb, int K, int seg_len,
+                                              long sub_stride, int n_tiles, Epi epi) {
         const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
         const int wa = wave / WB, wb = wave % WB, lr = lane & 31, lh = lane >> 5;
-        const int nk = (K + BK - 1) / BK, ns = nk * n_tiles;
-        const uint32_t tail = (nk - 1) * BK + RowsA::chunk() * 8 < K ? 0u : RING_RECORDS;
+        const int seg_k = seg_len > 0 ? seg_len : K, n_seg = K / seg_k;
+        const int sps = (seg_k + BK - 1) / BK, nk = sps * n_seg, ns = nk * n_tiles;   // steps per segment, tile and call
+        const uint32_t tail = (sps - 1) * BK + RowsA::chunk() * 8 < seg_k ? 0u : RING_RECORDS;
         RowsA ra;
         load_a(ra, 0);
-        int iu = 0, ik = 0;   // tile and step of the next loads
+        int iu = 0, isg = 0, ik = 0;   // tile, segment and its step of the next loads
         auto issue = [&](int d, uint16_t *st, uint32_t oob) {
             if (d < CA) dma(ra, d, st + (wave + NW * d) * 512, ik * BK * 2, oob);
             else dma(rb, d - CA, st + BA * BK + (wave + NW * (d - CA)) * 512, ik * BK * 2, oob);
         };
         auto advance = [&]() {
-            if (++ik == nk) {
-                ik = 0;
+            if (++ik < sps) return;
+            ik = 0;
+            long by = sub_stride;
+            if (++isg == n_seg) {
+                isg = 0;
+                by = -(long)(n_seg - 1) * sub_stride;
                 if (++iu < n_tiles) load_a(ra, iu);
+            } else {
+#pragma unroll
+                for (int i = 0; i < CA; ++i) ra.base[i] += by;
             }
+#pragma unroll
+            for (int i = 0; i < CB; ++i) rb.base[i] += by;
         };
         int oa[4], ob[4];
 #pragma unroll
@@ -222,7 +233,7 @@ struct RingTile {
         for (int q = 0; q < NST; ++q)
             if (q < ns) {
 #pragma unroll
-                for (int d = 0; d < IPT; ++d) issue(d, lds + q * STAGE, ik + 1 < nk ? 0u : tail);
+                for (int d = 0; d < IPT; ++d) issue(d, lds + q * STAGE, ik + 1 < sps ? 0u : tail);
                 advance();
             }
         if (ns >= NST) {
@@ -247,7 +258,7 @@ struct RingTile {
                 OC_WAIT_VMCNT(0);
             }
             barrier_lds();
-            phase(std::false_type{}, 1, ot, 0, st, s + NST < ns, ik + 1 < nk ? 0u : tail);
+            phase(std::false_type{}, 1, ot, 0, st, s + NST < ns, ik + 1 < sps ? 0u : tail);
             if (s + NST < ns) advance();
             st = ot;
             if (++kt == nk) {

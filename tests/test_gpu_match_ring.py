@@ -83,3 +83,24 @@ def test_frame_pairs(F, H, W, C, k, r_frame):
                                     weights_dev(wl), weights_f64(wl), case=f"pairs {F} {k}")
         print(f"  step {s}: {st}", flush=True)
         ora, valid = res.y, True
+
+
+@pytest.mark.parametrize("F,H,W,C,k", [
+    (4, 16, 24, 64, 1),      # one K step per segment
+    (3, 32, 40, 128, 1),     # two, several representative tiles
+    (5, 24, 16, 192, 2),     # three, patches
+    (7, 64, 56, 64, 4),      # enough tiles that K is not split
+])
+def test_blocks(F, H, W, C, k):
+    print(f"blocks F={F} {H}x{W} C={C} k={k}", flush=True)
+    wl = small_workload("block", F=F, H=H, W=W, C=C, heads=C // 64, head_dim=64, dtype="bf16", r=0.5, patch_k=k,
+                        n_steps=2, seed=78)
+    sh, cf, osh, ocf = shapes(wl)
+    dev = torch.device("cuda:0")
+    ws, cache = oc.workspace(sh, cf, dev), oc.LayerCache(sh, dev)
+    ora, valid = None, False
+    for s in range(2):
+        res, st = layer_step_parity(wl, wl.steps[s], sh, cf, osh, ocf, cache, ws, ora, valid, None, None,
+                                    weights_dev(wl), weights_f64(wl), case=f"blocks {F} {k}")
+        print(f"  step {s}: {st}", flush=True)
+        ora, valid = res.y, True
