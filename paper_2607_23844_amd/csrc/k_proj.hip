@@ -140,17 +140,27 @@ __global__ __launch_bounds__(RING_THREADS<ID>) void k_proj_qkv(
     ring_rows3(rb, wv, wv, wv, hd, hd, rm.C, f0);
     t.run(lds, ra, rb, rm.C);
     const int Lk = n_seq == 1 ? rm.n_rows : L;
-    if (seq_off == nullptr && (n_seq == 1 || L % BA == 0)) {
+    if (seq_off == nullptr && vt_whole_rows(n_seq, L, BA)) {
         const int s = n_seq == 1 ? 0 : r0 / L, j0 = r0 - s * L;   // j0 is a multiple of BA
+        const int end = vt_tile_end(j0, BA, Lk, lpad);
         stage_rows<BA>(t, lds, [&](float v, int a) { return (uint16_t)(j0 + a < Lk ? f2h_bits(v) : 0); },
                        [](int a) { return vt_key_of_pos(a); });
         __syncthreads();
-        write_rows<BA, BB, NT>(lds, min(BA, lpad - j0), [&](int b, int c0) -> uint16_t * {
+        const auto vt_at = [&](int b, int c0) -> uint16_t * {
             const int f = f0 + b;
             if (f >= hd) return nullptr;
             const int h = f / dh, d = f - h * dh;
             return Vt + (((long)h * n_seq + s) * dh + d) * lpad + j0 + c0;
-        });
+        };
+        write_rows<BA, BB, NT>(lds, min(BA, end - j0), vt_at);
+        if constexpr (BA % 64 != 0) {
+            // the key padding past the tile of a sequence's last one
+            const int zc = max(end - j0 - BA, 0) >> 3;
+            for (int c = threadIdx.x; c < BB * zc; c += NT) {
+                uint16_t *const at8 = vt_at(c / zc, BA + c % zc * 8);
+                if (at8 != nullptr) *reinterpret_cast<uint4 *>(at8) = make_uint4(0, 0, 0, 0);
+            }
+        }
         return;
     }
     // Tiles that cross sequences (or sequences whose starts are not multiples

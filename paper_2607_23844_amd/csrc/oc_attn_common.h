@@ -68,11 +68,18 @@ __device__ __forceinline__ int xcd_remap(int id, int total) {
 // inverse).  The attention kernel's PV operand is then one 16-byte read.
 __device__ __forceinline__ int vt_key_of_pos(int p) { return (p & ~12) | ((p & 4) << 1) | ((p & 8) >> 1); }
 
+// Vt rows as the tiles of the V projection (BA batch rows each) write them.
+// Tiles inside one sequence write runs of whole rows: the tile at position j0
+// writes [j0, vt_tile_end), which for a sequence's last one is the whole
+// padding; tiles across sequences store their tokens and zero the padding
+// separately.  (Tiles of 96 and 160 rows can end 32 positions short of lpad, a
+// multiple of 64.)
+__host__ __device__ inline bool vt_whole_rows(int n_seq, int L, int BA) { return n_seq == 1 || L % BA == 0; }
+__host__ __device__ inline int vt_tile_end(int j0, int BA, int Lk, int lpad) { return j0 + BA >= Lk ? lpad : j0 + BA; }
+
 // Whether the attention kernel may stage K/V by DMA for this head dim and
 // key count (head dims that are not a multiple of 64 take it only for grids
-// of eight-wave blocks).  The attention relies on the V projection having
-// zeroed the padded key positions [Lk, lpad) of every Vt row (but for
-// sequences of varying length).
+// of eight-wave blocks).
 // (buffer offsets of K are 32-bit: Lk * hd * 2 bytes must stay below 2^31)
 inline bool flash_uses_dma(int dh, int Lk, int hd) {
     return dh % 8 == 0 && dh <= 128 && Lk >= 256 && (long)Lk * hd * 2 < (1L << 31);
