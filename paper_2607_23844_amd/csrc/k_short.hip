@@ -63,12 +63,18 @@ __global__ __launch_bounds__(256) void k_qkv_attn_short(RowMap rm, const uint16_
         ra.base[i] = w + (long)(h * SH_DH + (a8 & (SH_DH - 1))) * C;
         ra.off[i] = ((threadIdx.x & 63) >> 3) * (uint32_t)(C * 2) + (uint32_t)ra.chunk() * 16;
     }
+    // (listed rows lie in a tensor below 2^31 elements, which 32-bit byte
+    // offsets reach; a batch of its own may be larger, so its rows are read
+    // behind the tile's first one)
+    const bool listed = rm.row_idx != nullptr || rm.tF > 0;
+    const uint16_t *const xb = listed ? rm.x : rm.x + (long)seq0 * L * C;
 #pragma unroll
     for (int i = 0; i < T::CB; ++i) {
         // (slots without a token repeat the tile's first one)
-        const int b = rb.row(i), r = seq0 * L + (b < n_slots ? b : 0);
-        rb.base[i] = rm.x;
-        rb.off[i] = (uint32_t)batch_token(r, rm.row_idx, rm.tF, rm.tN) * (uint32_t)(C * 2) + (uint32_t)rb.chunk() * 16;
+        const int b = rb.row(i), r = b < n_slots ? b : 0;
+        const int tok = listed ? (int)batch_token(seq0 * L + r, rm.row_idx, rm.tF, rm.tN) : r;
+        rb.base[i] = xb;
+        rb.off[i] = (uint32_t)tok * (uint32_t)(C * 2) + (uint32_t)rb.chunk() * 16;
     }
     T t;
     t.run(lds, ra, rb, C);
