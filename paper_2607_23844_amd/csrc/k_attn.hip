@@ -108,12 +108,14 @@ constexpr int FA_WAVES = 8, FA_KEYS = 32, FA_LD = 20;
 template <int NKS>   // 16-element steps of the head dim
 __global__ __launch_bounds__(FA_WAVES * 64) void k_attn_f32(const float *__restrict__ Q, const float *__restrict__ K,
                                                             const float *__restrict__ V, float *__restrict__ O,
-                                                            int heads, int dh, int L, int Lk, int n_qt, float scale,
+                                                            int heads, int dh, int n_seq, int L, int Lk, int n_qt,
+                                                            float scale,
                                                             const int32_t *__restrict__ seq_off) {
     constexpr int MAXW = NKS <= 4 ? FA_WAVES : FA_WAVES / 2;   // (the launch uses at most these)
     __shared__ float so[MAXW * NKS * 16 * FA_LD];
     __shared__ float sm[MAXW][16], sl[MAXW][16];
-    const int qt = blockIdx.x % n_qt, hs = blockIdx.x / n_qt, h = hs % heads, s = hs / heads;
+    const int id = (int)folded_block(), qt = id % n_qt, hs = id / n_qt, h = hs % heads, s = hs / heads;
+    if (s >= n_seq) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
     const int lr = lane & 15, lg = lane >> 4;
     const int hd = heads * dh;
@@ -258,9 +260,9 @@ static hipError_t go_attn_f32(const Plan &p, const AttnArgs &a, int Lk, hipStrea
     const int n_qt = cdiv(Lk, 16);
     const long blocks = (long)n_qt * p.heads * a.n_seq;
     if (blocks >= (1L << 31)) return hipErrorInvalidValue;
-    launch_k(k_attn_f32<NKS>, (unsigned)blocks, nw * 64, 0, st, (const float *)a.q, (const float *)a.k,
-             (const float *)a.vt, (float *)a.o, p.heads, p.dh, a.L, Lk, n_qt, (float)(1.0 / sqrt((double)p.dh)),
-             a.seq_off);
+    launch_k(k_attn_f32<NKS>, folded_grid(blocks, nw * 64), nw * 64, 0, st, (const float *)a.q, (const float *)a.k,
+             (const float *)a.vt, (float *)a.o, p.heads, p.dh, a.n_seq, a.L, Lk, n_qt,
+             (float)(1.0 / sqrt((double)p.dh)), a.seq_off);
     return hipGetLastError();
 }
 

@@ -572,13 +572,14 @@ __global__ __launch_bounds__(256) void k_match_part_reduce(const float *__restri
 // 768 x 256 x 320 on 12 blocks; the tiles take 8.1).
 template <typename T, int BA, int BB>
 __global__ __launch_bounds__(256) void k_match_f32(const float *__restrict__ x, const float *__restrict__ inv,
-                                                   GroupMap gm, int S, int D, int K, int seg_len, long sub_stride,
-                                                   long item_stride, int n_bt, int n_at,
+                                                   GroupMap gm, int G, int S, int D, int K, int seg_len,
+                                                   long sub_stride, long item_stride, int n_bt, int n_at,
                                                    unsigned long long *__restrict__ node_pack) {
     extern __shared__ __align__(16) float ldsf[];
     __shared__ float sinv[BA], sv[2][BB];
     __shared__ int si[2][BB];
-    const int at = blockIdx.x % n_at, bt = (blockIdx.x / n_at) % n_bt, g = blockIdx.x / (n_at * n_bt);
+    const int id = (int)folded_block(), at = id % n_at, bt = (id / n_at) % n_bt, g = id / (n_at * n_bt);
+    if (g >= G) return;
     const GroupMap::Grp gr = gm.group(g);
     if (bt * BB >= gr.nsrc) return;
     const float *rowsA[T::NA], *rowsB[T::NB];
@@ -747,8 +748,9 @@ static hipError_t go_match_f32(const Plan &p, const float *x, const float *inv, 
     const int S = p.n_src_max, D = p.n_dst_max, n_bt = cdiv(S, B), n_at = cdiv(D, B);
     const hipError_t e = allow_lds(k_match_f32<T, B, B>, T::LDS_BYTES);
     if (e != hipSuccess) return e;
-    launch_k(k_match_f32<T, B, B>, n_bt * n_at * p.n_groups, 256, T::LDS_BYTES, st, x, inv, gm, S, D, mg.K,
-             mg.seg_len, mg.sub_stride, mg.item_stride, n_bt, n_at, node_pack);
+    const long blocks = (long)n_bt * n_at * p.n_groups;
+    if (blocks >= (1L << 30)) return hipErrorInvalidValue;   // (2^28 tokens in the largest groups give a quarter)
+    launch_k(k_match_f32<T, B, B>, folded_grid(blocks, 256), 256, T::LDS_BYTES, st, x, inv, gm, p.n_groups, S, D, mg.K, mg.seg_len, mg.sub_stride, mg.item_stride, n_bt, n_at, node_pack);
     return hipGetLastError();
 }
 

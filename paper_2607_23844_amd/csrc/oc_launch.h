@@ -7,8 +7,22 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 #include "oc_internal.h"
+#include <algorithm>
 
 namespace oc {
+
+// A grid holds fewer than 2^32 threads along a dimension; HIP drops the blocks
+// past that without an error.
+constexpr long MAX_GRID_THREADS = 1L << 32;
+
+// Launches that may need more: `blocks` blocks (below 2^31) of `threads`
+// threads in rows of x, numbered by folded_block() (the last row may go past
+// the last block).
+inline dim3 folded_grid(long blocks, int threads) {
+    const long x = std::min(blocks, MAX_GRID_THREADS / 2 / threads);
+    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+__device__ __forceinline__ unsigned folded_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
 
 // An event pair for the next launch on st when a stage is being timed.
 bool timed_launch_events(hipStream_t st, hipEvent_t *start, hipEvent_t *stop);

@@ -26,6 +26,7 @@
 // reads as zero.
 #pragma once
 #include "oc_mfma_tile.h"
+#include "oc_launch.h"
 #include <type_traits>
 
 namespace oc {
@@ -349,14 +350,21 @@ inline float ring_cost(const RingShapeCost &c, int nk, long blocks, float epi = 
     return t;
 }
 
-// The shape with the lowest cost for K elements; tiles(BA, BB): tiles of the launch.
+// The shape with the lowest cost for K elements; tiles(BA, BB): tiles of the
+// launch.  Not more threads than a grid holds (the narrow shapes, on half a
+// billion rows of few columns); room for the blocks that convert weights.
 template <typename Tiles>
 inline int ring_pick(int K, Tiles tiles) {
+    constexpr int threads[N_RING_SHAPES] = {RING_THREADS<0>, RING_THREADS<1>, RING_THREADS<2>, RING_THREADS<3>,
+                                            RING_THREADS<4>, RING_THREADS<5>, RING_THREADS<6>, RING_THREADS<7>,
+                                            RING_THREADS<8>, RING_THREADS<9>};
     const int nk = (K + 63) / 64;
     int best = 0;
     float best_t = 0.f;
     for (int i = 0; i < N_RING_SHAPES; ++i) {
-        const float t = ring_cost(RING_SHAPES[i], nk, tiles(RING_SHAPES[i].BA, RING_SHAPES[i].BB));
+        const long n = tiles(RING_SHAPES[i].BA, RING_SHAPES[i].BB);
+        if (i > 0 && (n + 1024) * threads[i] >= MAX_GRID_THREADS) continue;
+        const float t = ring_cost(RING_SHAPES[i], nk, n);
         if (i == 0 || t < best_t) {
             best = i;
             best_t = t;

@@ -3,9 +3,6 @@ that stages keys by DMA multiplies whole 64-key tiles, so every position of
 [0, lpad) has to be written by the projection, whatever the workspace held.
 The cases are calls whose projection takes tiles of 96 or 160 rows, which end
 32 positions short of lpad."""
-import os
-import subprocess
-
 import numpy as np
 import pytest
 import torch
@@ -28,22 +25,9 @@ CASES = [   # heads, head dim, C, sequences, tokens, context; rows of the projec
 ]
 
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-
-
-@pytest.fixture(scope="module")
-def cover(tmp_path_factory):
-    """tests/native/vt_cover.cpp, built against the library's own rules."""
-    exe = str(tmp_path_factory.mktemp("native") / "vt_cover")
-    lib = os.path.join(ROOT, "paper_2607_23844_amd")
-    for cmd in (["/opt/rocm/bin/hipcc", "-x", "hip", "--cuda-host-only", "--offload-arch=gfx950", "-fPIC", "-O1", "-std=c++17",
-                 "-I", os.path.join(ROOT, "include"), "-I", os.path.join(lib, "csrc"), "-c",
-                 os.path.join(ROOT, "tests", "native", "vt_cover.cpp"), "-o", exe + ".o"],
-                ["g++", exe + ".o", "-o", exe, "-L", lib, "-loc", "-L/opt/rocm/lib", "-lamdhip64", f"-Wl,-rpath,{lib}",
-                 "-Wl,-rpath,/opt/rocm/lib"]):
-        r = subprocess.run(cmd, capture_output=True, text=True)
-        assert r.returncode == 0, r.stderr[-2000:]
-    return lambda *a: subprocess.run([exe, *map(str, a)], capture_output=True, text=True, timeout=60)
+@pytest.fixture
+def cover(native):
+    return native("vt_cover")
 
 
 def test_every_position_is_written(cover):
