@@ -418,16 +418,17 @@ __global__ __launch_bounds__(RING_THREADS<ID>) void k_match_ring(const uint16_t 
 #pragma unroll
                 for (int k = 0; k < 16; ++k) t[k] = tile.acc[i][j][k] * w[k];
                 if (!full) {
+                    // (padding: a NaN, which no maximum takes and no comparison finds)
 #pragma unroll
                     for (int k = 0; k < 16; ++k)
-                        if (w[k] < 0.f) t[k] = -INFINITY;
+                        if (w[k] < 0.f) t[k] = __builtin_nanf("");
                 }
                 float m4[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     m4[q] = fmaxf(fmaxf(fmaxf(t[4 * q], t[4 * q + 1]), t[4 * q + 2]), t[4 * q + 3]);
                 const float m = fmaxf(fmaxf(fmaxf(m4[0], m4[1]), m4[2]), m4[3]);
-                if (m > bv[j]) {
+                if (m >= bv[j]) {
                     float s0 = t[12], s1 = t[13], s2 = t[14];
                     int ix = base + 24;
 #pragma unroll
@@ -439,8 +440,9 @@ __global__ __launch_bounds__(RING_THREADS<ID>) void k_match_ring(const uint16_t 
                         ix = here ? base + 8 * q : ix;
                     }
                     ix += s0 == m ? 0 : s1 == m ? 1 : s2 == m ? 2 : 3;
+                    // (an equal value replaces none but the start: products of -inf only)
+                    bi[j] = m > bv[j] || bi[j] < 0 ? ix : bi[j];
                     bv[j] = m;
-                    bi[j] = ix;
                 }
             }
         }

@@ -104,3 +104,35 @@ def test_blocks(F, H, W, C, k):
                                     weights_dev(wl), weights_f64(wl), case=f"blocks {F} {k}")
         print(f"  step {s}: {st}", flush=True)
         ora, valid = res.y, True
+
+
+@pytest.mark.parametrize("F,H,W,C,k", [
+    (2, 16, 24, 64, 1),      # one ragged tile of representatives
+    (2, 40, 36, 72, 1),      # several tiles, the last one ragged
+    (1, 32, 32, 64, 4),      # patches of 16 representatives
+    (16, 72, 72, 128, 1),    # 256 x 256 tiles, six per block
+])
+def test_infinite_and_nan_candidates(F, H, W, C, k):
+    """A candidate whose every product is -inf is matched to the first
+    representative of its group (equal values: the smallest id), one whose
+    products are NaN to none, and neither touches its neighbours."""
+    print(f"match, infinite candidates F={F} {H}x{W} C={C} k={k}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(F * 1000 + C)
+    x = torch.randn(F, H, W, C, generator=g, device="cuda")
+    x[:, ::2, ::2, 0] = -x[:, ::2, ::2, 0].abs() - 0.5      # every representative: a negative first channel
+    sh, cf = oc.Shape(F, H, W, C, 1, 16, 0, "bf16"), oc.Cfg("token", r=0.5, patch_k=k)
+    pl = oc.plan(sh, cf)
+    ws = oc.workspace(sh, cf, x.device)
+    clean = oc.match(x.bfloat16().view(F, H * W, C), sh, cf, ws)
+    y = x.clone()
+    y[F - 1, H - 1, W - 1, 0] = float("inf")                # the last candidate of the last group
+    y[0, 0, 1, 0] = float("inf")                            # the first of the first
+    y[0, 0, 3, 1] = float("nan")
+    nm, ni = oc.match(y.bfloat16().view(F, H * W, C), sh, cf, ws)
+    ni, was = ni.view(-1, pl.n_src_max), clean[1].view(-1, pl.n_src_max)
+    ph, pw = H // k, W // k
+    assert int(ni[0, 0]) == 0
+    assert int(ni[-1, -1]) == (F - 1) * H * W + (k - 1) * ph * W + (k - 1) * pw
+    assert int(ni[0, 1]) == -1
+    changed = (ni != was).nonzero().tolist()
+    assert all(c in ([0, 0], [0, 1], [ni.shape[0] - 1, pl.n_src_max - 1]) for c in changed), changed[:8]
