@@ -15,12 +15,12 @@ namespace oc {
 
 constexpr int CMP_THREADS = 1024;
 
-// Frame pairs and unmatched frames (Frame+Token Cache), chunked: a frame's tokens in chunks of CMP_THREADS (one per
-// thread).  k_chunk_counts counts each chunk's cached tokens; block (unit u,
-// chunk q) of k_compact_chunks then takes its bases from those counts (kept
-// rows before it in its unit, cached tokens before it in id order) and its
-// in-chunk ranks from per-wave ballots.  A unit's chunks are those of frame
-// fa, then those of frame fb (pairs).
+// Frame pairs and unmatched frames (Frame+Token Cache), chunked: a frame's
+// tokens in chunks of CMP_THREADS (one per thread).  k_chunk_counts counts
+// each chunk's cached tokens; block (unit u, chunk q) of k_compact_chunks then
+// takes its bases from those counts (kept rows before it in its unit, cached
+// tokens before it in id order) and its in-chunk ranks from per-wave ballots.
+// A unit's chunks are those of frame fa, then those of frame fb (pairs).
 __global__ __launch_bounds__(CMP_THREADS) void k_chunk_counts(const int32_t *__restrict__ flag, int N, int nch,
                                                               int32_t *__restrict__ ccnt) {
     __shared__ int wsum[CMP_THREADS / 64];
@@ -95,10 +95,16 @@ __global__ __launch_bounds__(CMP_THREADS) void k_compact_chunks(const int32_t *_
 }
 
 // Cached items among the first n (n a multiple of 64): every thread adds a
-// strided share, the block sums.  red: one int per wave.
-__device__ __forceinline__ int cached_before(const int32_t *__restrict__ flag, int n, int *red) {
-    int c = 0;
-    for (int i = threadIdx.x * 4; i < n; i += blockDim.x * 4) {
+// strided share, the block sums.  ccnt, when given, holds the counts of whole
+// chunks.  red: one int per wave.
+__device__ __forceinline__ int cached_before(const int32_t *__restrict__ flag, const int32_t *__restrict__ ccnt, int n,
+                                             int *red) {
+    int c = 0, i0 = 0;
+    if (ccnt != nullptr) {
+        for (int e = threadIdx.x; e < n / CMP_THREADS; e += blockDim.x) c += ccnt[e];
+        i0 = n / CMP_THREADS * CMP_THREADS;
+    }
+    for (int i = i0 + threadIdx.x * 4; i < n; i += blockDim.x * 4) {
         const int4 v = *reinterpret_cast<const int4 *>(flag + i);
         c += (v.x != 0) + (v.y != 0) + (v.z != 0) + (v.w != 0);
     }
@@ -113,21 +119,22 @@ __device__ __forceinline__ int cached_before(const int32_t *__restrict__ flag, i
 
 // Token Cache (no frame pairs): every frame caches the same number of tokens,
 // so a chunk's bases follow from the cached tokens before it in its own frame,
-// which its block counts itself (at most N flags, in L2): one launch instead
-// of a counting and a writing one (8.1 -> 4.1 us on 4096 tokens in 2 x 2
-// patches).  Rows [f*L, f*L+L) and cached ranks [f*(N-L), ...) of frame f.
-__global__ __launch_bounds__(CMP_THREADS) void k_compact_tokens(const int32_t *__restrict__ flag, int N, int nch,
+// which its block counts itself (at most N flags, in L2) or, for many tokens,
+// takes from the chunk counts (ccnt).  Rows [f*L, f*L+L) and cached ranks
+// [f*(N-L), ...) of frame f.
+__global__ __launch_bounds__(CMP_THREADS) void k_compact_tokens(const int32_t *__restrict__ flag,
+                                                                const int32_t *__restrict__ ccnt, int N, int nch,
                                                                 int L, int32_t *__restrict__ kept_idx,
                                                                 int32_t *__restrict__ cached_idx,
                                                                 int32_t *__restrict__ rmap) {
     __shared__ int red[CMP_THREADS / 64], wcnt[CMP_THREADS / 64];
     const int f = blockIdx.x / nch, c0 = (blockIdx.x - f * nch) * CMP_THREADS;
-    const int32_t *fl = flag + (long)f * N;
+    const int32_t *fl = flag + (long)f * N, *cc = ccnt != nullptr ? ccnt + (long)f * nch : nullptr;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, i = c0 + t;
     const bool cached = i < N && fl[i] != 0;
     const unsigned long long b = __builtin_amdgcn_ballot_w64(cached);
     if (lane == 0) wcnt[wave] = __builtin_popcountll(b);
-    int crank = cached_before(fl, c0, red);   // (its barrier also publishes wcnt)
+    int crank = cached_before(fl, cc, c0, red);   // (its barrier also publishes wcnt)
     if (i >= N) return;
     for (int w = 0; w < wave; ++w) crank += wcnt[w];
     crank += __builtin_popcountll(b & ((1ull << lane) - 1ull));
@@ -144,16 +151,17 @@ __global__ __launch_bounds__(CMP_THREADS) void k_compact_tokens(const int32_t *_
 // Block kind: the b-th retained position (ascending) becomes sequence b with
 // rows b*F + f; cached tokens ascend frame-major.  One block per CB_POS
 // positions, all their frames: it counts the cached positions before its own
-// (N flags at most, in L2), ranks its positions and writes runs of
-// consecutive rows.  (One block for everything took 167 us on 9216 positions
-// of 25 frames, 6 us this way.)
+// (N flags at most, in L2, or the chunk counts), ranks its positions and
+// writes runs of consecutive rows.  (One block for everything took 167 us on
+// 9216 positions of 25 frames, 6 us this way.)
 constexpr int CB_POS = 64;
-__global__ __launch_bounds__(256) void k_compact_blocks(const int32_t *__restrict__ flag, int F, int N, int n_seq,
+__global__ __launch_bounds__(256) void k_compact_blocks(const int32_t *__restrict__ flag,
+                                                        const int32_t *__restrict__ ccnt, int F, int N, int n_seq,
                                                         int32_t *__restrict__ kept_idx,
                                                         int32_t *__restrict__ cached_idx, int32_t *__restrict__ rmap) {
     __shared__ int red[4], kept_n[CB_POS];
     const int n0 = blockIdx.x * CB_POS, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c0 = cached_before(flag, n0, red), n_cb = N - n_seq;
+    const int c0 = cached_before(flag, ccnt, n0, red), n_cb = N - n_seq;
     // every wave ranks the block's 64 positions (lane -> position)
     const int n = n0 + lane;
     const bool cached = n < N && flag[n] != 0;
@@ -327,28 +335,38 @@ hipError_t launch_compact_fpatch(const Plan &p, const int32_t *flag, const int32
     return hipGetLastError();
 }
 
+// Tokens of a frame (positions of a temporal layer) up to which the blocks of
+// the compaction count the flags before their own: one launch instead of two
+// (Token Cache, us in one launch / with chunk counts: 4096 tokens 4.2 / 8.9,
+// 32768 7.7 / 10.0, 65536 11.3 / 9.4, 262144 26 / 9.5, 1048576 98 / 16).
+constexpr int CMP_COUNT_N = 32768;
+
 hipError_t launch_compact(const Plan &p, const int32_t *units, const int32_t *flag, const int32_t *mtok,
                           int32_t *fcnt, int32_t *kept_idx, int32_t *cached_idx, int32_t *rmap, int map_matched,
                           hipStream_t st) {
     const long total = (long)p.F * p.N;
     const unsigned grid = (unsigned)std::min<long>((total + 255) / 256, 4096);
+    const int nch = cdiv(p.N, CMP_THREADS);
+    const int32_t *const ccnt = p.N > CMP_COUNT_N ? fcnt : nullptr;
     if (p.kind == KIND_TOKEN) {
         // frame pairs: chunk counts, then every (unit, chunk) block from them
-        const int nch = cdiv(p.N, CMP_THREADS);
         const bool pairs = p.gran == 3;
         StageScope _stage(st, "compact");
-        if (!pairs) {
-            launch_k(k_compact_tokens, (unsigned)(p.F * nch), CMP_THREADS, 0, st, flag, p.N, nch, p.seq_len, kept_idx,
-                     cached_idx, rmap);
-        } else {
+        if (pairs || ccnt != nullptr)
             launch_k(k_chunk_counts, (unsigned)(p.F * nch), CMP_THREADS, 0, st, flag, p.N, nch, fcnt);
+        if (!pairs) {
+            launch_k(k_compact_tokens, (unsigned)(p.F * nch), CMP_THREADS, 0, st, flag, ccnt, p.N, nch, p.seq_len,
+                     kept_idx, cached_idx, rmap);
+        } else {
             launch_k(k_compact_chunks, (unsigned)(p.n_units * 2 * nch), CMP_THREADS, 0, st, units,
                      p.F, p.N, nch, flag, (const int32_t *)fcnt, p.seq_len, p.n_cached, kept_idx, cached_idx, rmap);
         }
     } else if (p.kind == KIND_BLOCK) {
         {
             StageScope _stage(st, "compact");
-            launch_k(k_compact_blocks, (unsigned)cdiv(p.N, CB_POS), 256, 0, st, flag, p.F, p.N, p.n_seq, kept_idx, cached_idx, rmap);
+            if (ccnt != nullptr) launch_k(k_chunk_counts, (unsigned)nch, CMP_THREADS, 0, st, flag, p.N, nch, fcnt);
+            launch_k(k_compact_blocks, (unsigned)cdiv(p.N, CB_POS), 256, 0, st, flag, ccnt, p.F, p.N, p.n_seq, kept_idx,
+                     cached_idx, rmap);
         }
     } else {
         {

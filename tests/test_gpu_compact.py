@@ -40,3 +40,50 @@ def test_compaction_chain(case):
         res, _ = layer_step_parity(wl, wl.steps[s], sh, cf, osh, ocf, cache, ws, ora, valid, None, None, W, W64,
                                    case="latte_spatial frame patches k2" if gran == "frame" else "")
         ora, valid = res.y, True
+
+
+@pytest.mark.parametrize("gran,F,H,W,k", [
+    ("token", 2, 256, 128, 4),     # 32768 tokens: the blocks count the flags before their own
+    ("token", 2, 256, 132, 2),     # 33792: from chunk counts
+    ("token", 1, 260, 132, 2),     # 34320, the last chunk partial
+    ("block", 3, 256, 128, 4),
+    ("block", 2, 260, 132, 2),
+    ("block", 1, 512, 256, 4),
+])
+def test_many_tokens(gran, F, H, W, k):
+    """The selection of many tokens against its definition, on random
+    similarities without ties."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"compaction of many tokens {gran} F={F} {H}x{W} k={k}", flush=True)
+    sh, cf = oc.Shape(F, H, W, 8, 1, 16, 0, "bf16"), oc.Cfg(gran, r=0.4, patch_k=k)
+    pl = oc.plan(sh, cf)
+    G, S, N = pl.n_groups, pl.n_src_max, H * W
+    g = torch.Generator(device="cuda").manual_seed(H)
+    nm = (torch.randperm(G * S, generator=g, device="cuda").float() / (G * S)).contiguous()
+    ni = torch.zeros(G * S, dtype=torch.int32, device="cuda")
+    kept, cached, rmap = oc.select(nm, ni, sh, cf, oc.workspace(sh, cf, nm.device))
+    # candidates of a patch: its tokens off the even rows and columns, ascending
+    ids = torch.arange(N, device="cuda").view(H, W)
+    ph, pw = H // k, W // k
+    R = int(0.4 * ph * pw)
+    Fg = F if gran == "token" else 1
+    flag = torch.zeros(Fg, N, dtype=torch.bool, device="cuda")
+    for f in range(Fg):
+        for p in range(k * k):
+            tile = ids[p // k * ph:(p // k + 1) * ph, p % k * pw:(p % k + 1) * pw]
+            cand = tile.reshape(-1)
+            cand = cand[((cand // W) % 2 == 1) | ((cand % W) % 2 == 1)]
+            flag[f, cand[nm[(f * k * k + p) * S:][:S].topk(R).indices]] = True
+    if gran == "token":
+        want_kept = (~flag).reshape(-1).nonzero().reshape(-1)
+        want_cached = flag.reshape(-1).nonzero().reshape(-1)
+    else:
+        pos = (~flag[0]).nonzero().reshape(-1)
+        want_kept = (torch.arange(F, device="cuda")[None, :] * N + pos[:, None]).reshape(-1)
+        want_cached = (torch.arange(F, device="cuda")[:, None] * N + flag[0].nonzero().reshape(-1)[None, :]).reshape(-1)
+    want_map = torch.full((F * N,), -1, dtype=torch.int64, device="cuda")
+    want_map[want_kept] = torch.arange(want_kept.numel(), device="cuda")
+    assert torch.equal(kept.long(), want_kept)
+    assert torch.equal(cached.long(), want_cached)
+    assert torch.equal(rmap.long(), want_map)
