@@ -90,7 +90,8 @@ __device__ __forceinline__ void to_f16(const uint4 *__restrict__ src, long n8, u
 // sequence (a single sequence, or L a multiple of the tile) are written as Vt
 // rows: the positions of the tile's tokens, zero for positions past the end
 // (the key padding up to lpad), in whole chunks.  Otherwise they are stored in
-// quads of tokens and the key padding is zeroed separately.  The blocks past
+// quads of tokens and the key padding is zeroed separately where the attention
+// reads it (zero_pad, vt_padding_read).  The blocks past
 // the tiles convert wo for the output projection where no earlier launch of
 // the call has (the uncached layer and the attention entry point: a launch of
 // its own took 4.5 us of 263 on the SD3-like layer, 4.4 of 220 by stages).
@@ -99,7 +100,7 @@ template <int ID>
 __global__ __launch_bounds__(RING_THREADS<ID>) void k_proj_qkv(
     RowMap rm, const uint16_t *__restrict__ wq, const uint16_t *__restrict__ wk, const uint16_t *__restrict__ wv,
     int hd, int dh, float qscale, int nw, int n_qk_at, int n_bt, int n_v_at, int n_v_bt, int n_seq, int L, int lpad,
-    const int32_t *__restrict__ seq_off, uint16_t *__restrict__ Q, uint16_t *__restrict__ K,
+    int zero_pad, const int32_t *__restrict__ seq_off, uint16_t *__restrict__ Q, uint16_t *__restrict__ K,
     uint16_t *__restrict__ Vt, const uint4 *__restrict__ wo, long n8, uint4 *__restrict__ wo16) {
     using T = typename RingShape<ID, false>::Tile;
     constexpr int BA = T::BA, BB = T::BB, NT = T::NT;
@@ -198,10 +199,9 @@ __global__ __launch_bounds__(RING_THREADS<ID>) void k_proj_qkv(
         }
     }
     // zero the padded key positions [Lk, lpad) of this block's features, for
-    // the sequences s = at, at + n_v_at, ... (the attention reads them; it masks
-    // the ends of sequences of varying length itself)
+    // the sequences s = at, at + n_v_at, ...
     const int npad = lpad - Lk;
-    if (seq_off == nullptr && npad > 0) {
+    if (zero_pad && npad > 0) {
         for (int sq = at; sq < n_seq; sq += n_v_at)
             for (int idx = threadIdx.x; idx < BB * npad; idx += NT) {
                 const int f = f0 + idx / npad, jj = Lk + idx % npad;
@@ -218,6 +218,7 @@ hipError_t launch_proj_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a, h
     const int Lk = a.n_seq == 1 ? rm.n_rows : a.L;
     // short sequences: V rows from the Q/K tiles (nw = 3), no V tiles
     const int nw = a.seq_off == nullptr && attn_short(Lk) ? 3 : 2;
+    const int zero_pad = vt_padding_read(p, a, Lk) ? 1 : 0;
     const auto v_at = [&](int BA) { return nw == 3 ? 0 : cdiv(rm.n_rows, BA); };
     const long n8 = a.wo16_ready ? 0 : (long)p.C * p.hd / 8;
     const int id = ring_pick(p.C, [&](int BA, int BB) {
@@ -233,7 +234,7 @@ hipError_t launch_proj_qkv(const Plan &p, const RowMap &rm, const AttnArgs &a, h
         const int cvt_blocks = (int)std::min<long>((n8 + 4 * T::NT - 1) / (4 * T::NT), N_CUS);
         launch_k(k_proj_qkv<ID>, n_qk_at * n_bt + n_v_at * n_v_bt + cvt_blocks, T::NT, T::LDS_BYTES, st, rm,
                  (const uint16_t *)a.wq, (const uint16_t *)a.wk, (const uint16_t *)a.wv, p.hd, p.dh, qscale, nw,
-                 n_qk_at, n_bt, n_v_at, n_v_bt, a.n_seq, a.L, a.lpad, a.seq_off, (uint16_t *)a.q, (uint16_t *)a.k,
+                 n_qk_at, n_bt, n_v_at, n_v_bt, a.n_seq, a.L, a.lpad, zero_pad, a.seq_off, (uint16_t *)a.q, (uint16_t *)a.k,
                  (uint16_t *)a.vt, (const uint4 *)a.wo, n8, (uint4 *)a.wo16);
         return hipGetLastError();
     });

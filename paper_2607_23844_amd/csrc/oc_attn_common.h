@@ -71,9 +71,9 @@ __device__ __forceinline__ int vt_key_of_pos(int p) { return (p & ~12) | ((p & 4
 // Vt rows as the tiles of the V projection (BA batch rows each) write them.
 // Tiles inside one sequence write runs of whole rows: the tile at position j0
 // writes [j0, vt_tile_end), which for a sequence's last one is the whole
-// padding; tiles across sequences store their tokens and zero the padding
-// separately.  (Tiles of 96 and 160 rows can end 32 positions short of lpad, a
-// multiple of 64.)
+// padding; tiles across sequences store their tokens and, where it is read,
+// zero the padding separately.  (Tiles of 96 and 160 rows can end 32 positions
+// short of lpad, a multiple of 64.)
 __host__ __device__ inline bool vt_whole_rows(int n_seq, int L, int BA) { return n_seq == 1 || L % BA == 0; }
 __host__ __device__ inline int vt_tile_end(int j0, int BA, int Lk, int lpad) { return j0 + BA >= Lk ? lpad : j0 + BA; }
 
@@ -104,6 +104,14 @@ hipError_t launch_proj_out(const Plan &p, int n_rows, const AttnArgs &a, hipStre
 // share out the keys (k_flash_split.hip), where flash_splits says so
 bool flash_splits(const Plan &p, const AttnArgs &a, int Lk);
 hipError_t launch_flash_split(const Plan &p, const AttnArgs &a, int Lk, hipStream_t st);
+// Whether the attention reads the key padding of Vt rows unmasked: the kernels
+// that stage V by DMA and those that share out the keys do; the
+// register-staged ones, and all for sequences of varying length, mask the end
+// themselves.  (Zeroed for them too, tiles across sequences took 204 us instead
+// of 155 for 1450 sequences of 65 keys, 4 heads of 48, C = 192.)
+inline bool vt_padding_read(const Plan &p, const AttnArgs &a, int Lk) {
+    return a.seq_off == nullptr && (flash_splits(p, a, Lk) || flash_uses_dma(p.dh, Lk, p.hd));
+}
 hipError_t launch_flash(const Plan &p, const AttnArgs &a, int Lk, hipStream_t st);
 
 }  // namespace oc

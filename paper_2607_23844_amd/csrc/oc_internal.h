@@ -53,11 +53,10 @@ struct Layout {
 
 // Attention workspace carved at `base`: Q, K, O [rows, H*dh] and V
 // (bf16: Vt [H][seq][dh][lpad]; fp32: [rows, H*dh]).  lpad is the keys of a
-// sequence rounded up to 64.  The attention multiplies whole tiles of up to 64
-// keys by probabilities that are 0 past a sequence's end, so the projection
-// writes every position of [0, lpad), zeros past the end: whatever the
-// workspace held there may be a NaN.  (Sequences of varying length are the
-// exception: their attention masks the end of each itself.)
+// sequence rounded up to 64.  Kernels that multiply whole tiles of up to 64
+// keys by probabilities that are 0 past a sequence's end (vt_padding_read,
+// oc_attn_common.h) need every position of [0, lpad) written, zeros past the
+// end: what the workspace held there may be a NaN.
 struct AttnWs { size_t q, k, o, v, wo16, bytes; int lpad; };
 AttnWs attn_ws(const Plan &p, int n_seq, int L, size_t base);
 int gram_blocks(const Plan &p);

@@ -1,6 +1,6 @@
 // Simulates on the host which positions of the Vt rows the projection's tiles
 // write (the rules of oc_attn_common.h and the tile shapes of oc_ring_tile.h)
-// and reports the first call whose key padding is not covered.
+// and reports the first call whose key padding is read but not covered.
 //   vt_cover                             every tile shape over a grid of batches
 //   vt_cover heads dh C n_seq L n_ctx    tile rows, positions its tiles cover, lpad, and whether the DMA attention follows
 #include "oc_attn_common.h"
@@ -13,13 +13,13 @@
 using namespace oc;
 
 // first position of [0, lpad) that no write of a sequence covers, -1 if none
-static int uncovered(int BA, int n_seq, int L, int Lk, int lpad) {
+static int uncovered(int BA, int n_seq, int L, int Lk, int lpad, bool zero_pad) {
     std::vector<char> w(lpad, 0);
     if (vt_whole_rows(n_seq, L, BA)) {
         for (int j0 = 0; j0 < Lk; j0 += BA)
             for (int j = j0; j < vt_tile_end(j0, BA, Lk, lpad); ++j) w[j] = 1;
     } else {
-        for (int j = 0; j < lpad; ++j) w[j] = 1;   // tokens, then the zeroed padding [Lk, lpad)
+        for (int j = 0; j < (zero_pad ? lpad : Lk); ++j) w[j] = 1;   // tokens, then the zeroed padding
     }
     for (int j = 0; j < lpad; ++j)
         if (!w[j]) return j;
@@ -47,19 +47,25 @@ int main(int argc, char **argv) {
         return 0;
     }
     for (const RingShapeCost &c : RING_SHAPES)
-        for (int n_seq : {1, 2, 7})
-            for (int L = 1; L <= 2500; ++L)
-                for (int n_ctx : {0, 77}) {
-                    if (n_seq > 1 && n_ctx > 0) continue;
-                    Plan p;
-                    std::memset(&p, 0, sizeof(p));
-                    p.heads = 1; p.dh = 16; p.hd = 16; p.C = 64; p.n_ctx = n_ctx; p.bf16 = true; p.esz = 2;
-                    const int Lk = n_seq == 1 ? L + n_ctx : L, lpad = attn_ws(p, n_seq, L, 0).lpad;
-                    const int at = uncovered(c.BA, n_seq, L, Lk, lpad);
-                    if (at >= 0) {
-                        std::printf("tile of %d rows, %d x %d + %d: position %d of %d\n", c.BA, n_seq, L, n_ctx, at, lpad);
-                        return 1;
+        for (int heads : {1, 64})   // the keys shared out / staged by DMA
+            for (int n_seq : {1, 2, 7})
+                for (int L = 65; L <= 2500; ++L)
+                    for (int n_ctx : {0, 77}) {
+                        if (n_seq > 1 && n_ctx > 0) continue;
+                        Plan p;
+                        AttnArgs a;
+                        std::memset(&p, 0, sizeof(p));
+                        std::memset(&a, 0, sizeof(a));
+                        p.heads = heads; p.dh = 64; p.hd = heads * 64; p.C = 64; p.n_ctx = n_ctx; p.bf16 = true; p.esz = 2;
+                        a.n_seq = n_seq; a.L = L;
+                        const int Lk = n_seq == 1 ? L + n_ctx : L, lpad = attn_ws(p, n_seq, L, 0).lpad;
+                        const bool read = vt_padding_read(p, a, Lk);
+                        const int at = uncovered(c.BA, n_seq, L, Lk, lpad, read);
+                        if (read && at >= 0) {
+                            std::printf("tile of %d rows, %d heads, %d x %d + %d: position %d of %d\n", c.BA, heads, n_seq, L,
+                                        n_ctx, at, lpad);
+                            return 1;
+                        }
                     }
-                }
     return 0;
 }

@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     (64, 1, 64, 2, 272),      # starts 0 mod 16
     (64, 18, 64, 23, 133),    # 128 x 192 tiles (one round of them)
     (48, 2, 40, 9, 97),
+    (48, 4, 192, 100, 65),    # padding that the attention masks and nobody zeroes
+    (64, 6, 128, 20, 263),    # padding that the attention reads, staged by DMA
 ])
 def test_vt_across_sequences(dh, heads, C, n_seq, L):
     if not torch.cuda.is_available():
