@@ -221,16 +221,15 @@ hipError_t launch_tile_norm(const Plan &p, const void *x, float *inv, unsigned l
 // packed pair, so the representative tiles need no second pass.  The
 // representative norm is applied before the arg-max, the candidate's own
 // norm (a positive constant per row) when unpacking.
-template <int BA, int BB, int WA, int WB, bool DMA>
-using MatchTile = typename std::conditional<DMA, DmaTile<BA, BB, WA, WB>, MfmaTile<BA, BB, WA, WB>>::type;
-
-template <int BA, int BB, int WA, int WB, bool DMA>
+// Frame tiles (at most 16 representatives) and blocks whose channels are no
+// whole K steps.
+template <int BA, int BB, int WA, int WB>
 __global__ __launch_bounds__(256) void k_match_mfma(const uint16_t *__restrict__ x, const float *__restrict__ inv,
                                                      GroupMap gm, int G, int S, int D,
                                                      int K, int seg_len, long sub_stride, long item_stride,
                                                      int n_bt, int n_at,
                                                      unsigned long long *__restrict__ node_pack) {
-    using T = MatchTile<BA, BB, WA, WB, DMA>;
+    using T = MfmaTile<BA, BB, WA, WB>;
     extern __shared__ __align__(16) uint16_t lds[];
     const int total = n_bt * n_at * G;
     const int lid = xcd_remap(blockIdx.x, total);
@@ -252,10 +251,8 @@ __global__ __launch_bounds__(256) void k_match_mfma(const uint16_t *__restrict__
         rowsB[i] = id >= 0 ? x + (long)id * item_stride : nullptr;
     }
     T tile;
-    // rows without an item read x's first row (DMA) or zeros; either way
-    // their results are discarded below
-    if constexpr (DMA) tile.run(lds, rowsA, rowsB, x, x, K, seg_len, sub_stride);
-    else tile.run(lds, rowsA, rowsB, K, seg_len, sub_stride);
+    // rows without an item read zeros; their results are discarded below
+    tile.run(lds, rowsA, rowsB, K, seg_len, sub_stride);
 
     // representative norms of this tile (0 for padding, which never wins)
     float *sinv = reinterpret_cast<float *>(lds);
@@ -475,11 +472,11 @@ __global__ __launch_bounds__(RING_THREADS<ID>) void k_match_ring(const uint16_t 
 // raw dot products over its K range (whole 64-steps inside one segment) and
 // stores them to part[split][g][b][a]; k_match_part_reduce sums the splits in
 // order, applies the representative norms and takes the arg-max.
-template <int BA, int BB, int WA, int WB, bool DMA>
+template <int BA, int BB, int WA, int WB>
 __global__ __launch_bounds__(256) void k_match_part(const uint16_t *__restrict__ x, GroupMap gm, int G, int S, int D,
                                                      int kc, int seg_len, long sub_stride, long item_stride,
                                                      int n_bt, int n_at, int n_split, float *__restrict__ part) {
-    using T = MatchTile<BA, BB, WA, WB, DMA>;
+    using T = DmaTile<BA, BB, WA, WB>;
     extern __shared__ __align__(16) uint16_t lds[];
     const int total = n_bt * n_at * G * n_split;
     const int lid = xcd_remap(blockIdx.x, total);
@@ -504,8 +501,7 @@ __global__ __launch_bounds__(256) void k_match_part(const uint16_t *__restrict__
         rowsB[i] = id >= 0 ? x + (long)id * item_stride + off : nullptr;
     }
     T tile;
-    if constexpr (DMA) tile.run(lds, rowsA, rowsB, x, x, kc, 0, 0);
-    else tile.run(lds, rowsA, rowsB, kc, 0, 0);
+    tile.run(lds, rowsA, rowsB, x, x, kc);   // (rows without an item read x's first row)
     float *pp = part + ((long)sp * G + g) * S * D;
 #pragma unroll
     for (int j = 0; j < T::TB; ++j) {
@@ -659,18 +655,17 @@ static hipError_t allow_lds(KernelPtr k, size_t lds) {
     return raise_lds_limit((const void *)k, lds);
 }
 
-template <int BA, int BB, int WA, int WB, bool DMA>
-static hipError_t go_match(const Plan &p, const uint16_t *x, const float *inv, const GroupMap &gm, int K,
-                           int seg_len, long sub_stride, long item_stride, unsigned long long *node_pack,
-                           hipStream_t st) {
-    using T = MatchTile<BA, BB, WA, WB, DMA>;
+template <int BA, int BB, int WA, int WB>
+static hipError_t go_match(const Plan &p, const uint16_t *x, const float *inv, const GroupMap &gm, const MatchGeom &mg,
+                           unsigned long long *node_pack, hipStream_t st) {
+    using T = MfmaTile<BA, BB, WA, WB>;
     const int G = p.n_groups, S = p.n_src_max, D = p.n_dst_max;
     const int n_bt = cdiv(S, BB), n_at = cdiv(D, BA);
     const size_t lds = T::LDS_BYTES;
-    hipError_t e = allow_lds(k_match_mfma<BA, BB, WA, WB, DMA>, lds);
+    hipError_t e = allow_lds(k_match_mfma<BA, BB, WA, WB>, lds);
     if (e != hipSuccess) return e;
-    launch_k(k_match_mfma<BA, BB, WA, WB, DMA>, n_bt * n_at * G, 256, lds, st, x, inv, gm, G, S, D, K, seg_len,
-             sub_stride, item_stride, n_bt, n_at, node_pack);
+    launch_k(k_match_mfma<BA, BB, WA, WB>, n_bt * n_at * G, 256, lds, st, x, inv, gm, G, S, D, mg.K, mg.seg_len,
+             mg.sub_stride, mg.item_stride, n_bt, n_at, node_pack);
     return hipGetLastError();
 }
 
@@ -725,18 +720,18 @@ static hipError_t go_ring(const Plan &p, const uint16_t *x, const float *inv, co
     });
 }
 
-template <int BA, int BB, int WA, int WB, bool DMA>
+template <int BA, int BB, int WA, int WB>
 static hipError_t go_split(const Plan &p, const MatchSplit &ms, const uint16_t *x, const float *inv,
-                           const GroupMap &gm, int seg_len, long sub_stride, long item_stride, float *part,
-                           unsigned long long *node_pack, hipStream_t st) {
-    using T = MatchTile<BA, BB, WA, WB, DMA>;
+                           const GroupMap &gm, const MatchGeom &mg, float *part, unsigned long long *node_pack,
+                           hipStream_t st) {
+    using T = DmaTile<BA, BB, WA, WB>;
     const int G = p.n_groups, S = p.n_src_max, D = p.n_dst_max;
     const int n_bt = cdiv(S, BB), n_at = cdiv(D, BA);
     const size_t lds = T::LDS_BYTES;
-    hipError_t e = allow_lds(k_match_part<BA, BB, WA, WB, DMA>, lds);
+    hipError_t e = allow_lds(k_match_part<BA, BB, WA, WB>, lds);
     if (e != hipSuccess) return e;
-    launch_k(k_match_part<BA, BB, WA, WB, DMA>, n_bt * n_at * G * ms.n_split, 256, lds, st, x, gm, G, S, D, ms.kc,
-             seg_len, sub_stride, item_stride, n_bt, n_at, ms.n_split, part);
+    launch_k(k_match_part<BA, BB, WA, WB>, n_bt * n_at * G * ms.n_split, 256, lds, st, x, gm, G, S, D, ms.kc, mg.seg_len,
+             mg.sub_stride, mg.item_stride, n_bt, n_at, ms.n_split, part);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     launch_k(k_match_part_reduce, (unsigned)((long)G * S), 256, 0, st, (const float *)part, ms.n_split, G, S, D, inv,
@@ -752,7 +747,8 @@ static hipError_t go_match_f32(const Plan &p, const float *x, const float *inv, 
     if (e != hipSuccess) return e;
     const long blocks = (long)n_bt * n_at * p.n_groups;
     if (blocks >= (1L << 30)) return hipErrorInvalidValue;   // (2^28 tokens in the largest groups give a quarter)
-    launch_k(k_match_f32<T, B, B>, folded_grid(blocks, 256), 256, T::LDS_BYTES, st, x, inv, gm, p.n_groups, S, D, mg.K, mg.seg_len, mg.sub_stride, mg.item_stride, n_bt, n_at, node_pack);
+    launch_k(k_match_f32<T, B, B>, folded_grid(blocks, 256), 256, T::LDS_BYTES, st, x, inv, gm, p.n_groups, S, D,
+             mg.K, mg.seg_len, mg.sub_stride, mg.item_stride, n_bt, n_at, node_pack);
     return hipGetLastError();
 }
 
@@ -762,41 +758,25 @@ hipError_t launch_match(const Plan &p, const void *x, const float *inv, const in
     const GroupMap gm = group_map(p, units);
     const int G = p.n_groups, S = p.n_src_max, D = p.n_dst_max;
     const MatchGeom mg = match_geom(p);
-    const int K = mg.K;
-    const int seg_len = mg.seg_len;
-    const long sub_stride = mg.sub_stride;
-    const long item_stride = mg.item_stride;
     {
         StageScope _stage(st, "match");
         if (p.bf16) {
             const uint16_t *xb = (const uint16_t *)x;
             const MatchSplit ms = match_split(p);
-            const bool dma = K % 64 == 0 && (seg_len == 0 || seg_len % 64 == 0);
+            const bool steps = mg.K % 64 == 0 && mg.seg_len % 64 == 0;   // (of 64, whole in every segment)
             hipError_t e;
             if (ms.n_split > 1) {
                 // long descriptors, few tiles: split K (64-row tiles)
-                e = go_split<64, 64, 2, 2, true>(p, ms, xb, inv, gm, seg_len, sub_stride, item_stride, part,
-                                                 node_pack, st);
-            } else if (p.kind == KIND_TOKEN || (p.kind == KIND_BLOCK && dma)) {
+                e = go_split<64, 64, 2, 2>(p, ms, xb, inv, gm, mg, part, node_pack, st);
+            } else if (p.kind == KIND_TOKEN || (p.kind == KIND_BLOCK && steps)) {
                 e = go_ring(p, xb, inv, gm, mg, node_pack, st);
-            } else if (D > 64 && dma && (long)cdiv(D, 128) * cdiv(S, 64) * G < 2L * N_CUS) {
-                // a 128 x 64 grid under two blocks per CU: 64 x 64 tiles, three
-                // to five per CU (the SD3-like layer: 768 blocks, 20 against 23 us)
-                e = go_match<64, 64, 2, 2, true>(p, xb, inv, gm, K, seg_len, sub_stride, item_stride, node_pack,
-                                                 st);
             } else if (D > 64) {
-                // representative tile height by group size: 128, 64 or 32; large
-                // groups stream by LDS DMA when the K steps allow it
-                e = dma ? go_match<128, 64, 2, 2, true>(p, xb, inv, gm, K, seg_len, sub_stride, item_stride,
-                                                        node_pack, st)
-                        : go_match<128, 64, 2, 2, false>(p, xb, inv, gm, K, seg_len, sub_stride, item_stride,
-                                                         node_pack, st);
+                // representative tile height by group size: 128, 64 or 32
+                e = go_match<128, 64, 2, 2>(p, xb, inv, gm, mg, node_pack, st);
             } else if (D > 32) {
-                e = go_match<64, 64, 2, 2, false>(p, xb, inv, gm, K, seg_len, sub_stride, item_stride, node_pack,
-                                                  st);
+                e = go_match<64, 64, 2, 2>(p, xb, inv, gm, mg, node_pack, st);
             } else {
-                e = go_match<32, 128, 1, 4, false>(p, xb, inv, gm, K, seg_len, sub_stride, item_stride, node_pack,
-                                                   st);
+                e = go_match<32, 128, 1, 4>(p, xb, inv, gm, mg, node_pack, st);
             }
             if (e != hipSuccess) return e;
         } else {

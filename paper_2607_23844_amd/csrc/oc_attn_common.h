@@ -5,8 +5,6 @@
 
 namespace oc {
 
-// Batch row r of the reduced attention: x rows (through row_idx) then the
-// context rows.  nullptr past the end (a zero row for the tile loaders).
 // Batch row r (< n_main) -> token: through idx when given, else, for the
 // uncached temporal layer (tF > 0), the sequence-per-position order
 // r = n*tF + f -> token f*tN + n, else r itself.
@@ -19,15 +17,12 @@ __device__ __forceinline__ long batch_token(int r, const int32_t *idx, int tF, i
     return r;
 }
 
+// Batch rows of the reduced attention: n_main rows of x (through row_idx), then
+// the context rows.
 struct RowMap {
     const uint16_t *x; const int32_t *row_idx; int n_main;
     const uint16_t *ctx; int n_rows; int C;
     int tF, tN;
-    __device__ __forceinline__ const uint16_t *row(int r) const {
-        if (r >= n_rows) return nullptr;
-        if (r < n_main) return x + batch_token(r, row_idx, tF, tN) * C;
-        return ctx + (long)(r - n_main) * C;
-    }
 };
 
 // sequence and position of batch row r (a single sequence also owns the

@@ -5,20 +5,17 @@
 // staging registers).
 //
 // K is walked in steps of 64 through two LDS stages (small enough for two or
-// more blocks per CU): step kt+1 is loaded while step kt's MFMAs run.
-// An LDS row is the 128 bytes of one operand
-// row's step, unpadded; its 16-byte chunk c sits in slot c ^ ((row >> 1) & 7):
-// two rows fill the 64 LDS banks, so the fragment reads of 16 consecutive
-// rows hit distinct banks.  DMA
-// instruction i of a wave fills the 64 slots (wave + 4i)*64 .. +63 of the
+// more blocks per CU): step kt+1 is loaded while step kt's MFMAs run.  An LDS
+// row is the 128 bytes of one operand row's step, unpadded; its 16-byte chunk
+// c sits in slot c ^ ((row >> 1) & 7): two rows fill the 64 LDS banks, so the
+// fragment reads of 16 consecutive rows hit distinct banks.  DMA instruction i
+// of a wave fills the 64 slots (wave + 4i)*64 .. +63 of the
 // operand's stage, that is rows chunk_row(i) of MfmaTile: callers pass the
 // same per-thread row bases.  Rows without data (nullptr) read the fallback
 // row instead; their accumulators are garbage and must be discarded.
-// Requirements: K % 64 == 0, 16-byte aligned row bases; with segments
-// (seg_len > 0) seg_len % 64 == 0.
+// Requirements: K % 64 == 0, 16-byte aligned row bases.
 #pragma once
 #include "oc_mfma_tile.h"
-#include <type_traits>
 
 namespace oc {
 
@@ -72,8 +69,7 @@ struct DmaTile {
     // Full K loop.  rowsA[i] / rowsB[i]: this thread's row bases for
     // chunk_row(i) (nullptr: use the fallback row).
     __device__ __forceinline__ void run(uint16_t *lds, const uint16_t *const *rowsA, const uint16_t *const *rowsB,
-                                        const uint16_t *fallbackA, const uint16_t *fallbackB, int K, int seg_len,
-                                        long sub_stride) {
+                                        const uint16_t *fallbackA, const uint16_t *fallbackB, int K) {
         const int t = threadIdx.x, wave = t >> 6;
 #pragma unroll
         for (int i = 0; i < TA; ++i)
@@ -93,12 +89,7 @@ struct DmaTile {
         }
         const int nk = K / BK;
         auto issue = [&](int kt) {
-            const int k0 = kt * BK;
-            long off = k0;
-            if (seg_len > 0) {
-                const int s = k0 / seg_len;
-                off = (long)s * sub_stride + (k0 - s * seg_len);
-            }
+            const int off = kt * BK;
             uint16_t *st = lds + (kt & 1) * STAGE;
 #pragma unroll
             for (int i = 0; i < CA; ++i)

@@ -5,7 +5,6 @@
 #include "oc_launch.h"
 #include "oc_device.h"
 #include "oc_mfma_tile.h"
-#include "oc_dma_tile.h"
 
 namespace oc {
 

@@ -1,12 +1,12 @@
-// LDS-staged MFMA tile engine for gfx950 (bf16 or fp16 operands, fp32
-// accumulation in VGPRs).
+// LDS-staged MFMA tile engine for gfx950 (bf16 operands, fp32 accumulation in
+// VGPRs), and the 16-bit types and conversions of all engines.
 //
 // Computes a BA x BB block of  C[b][a] = sum_k A[a][k] * B[b][k]  where both
 // operands are K-contiguous rows (the "NT" form: token rows times
 // linear-layer weight rows, or candidate rows times representative rows).
 // 256 threads = 4 wave64s arranged WA x WB; each wave owns a
 // (BA/WA) x (BB/WB) sub-block of 32x32 accumulators of
-// v_mfma_f32_32x32x16_{bf16,f16}.
+// v_mfma_f32_32x32x16_bf16.
 //
 // MFMA operand layout (32x32x16): lane l feeds row/column (l % 32) and the 8
 // consecutive k of chunk (l / 32).  The result lane l holds column
@@ -18,9 +18,7 @@
 // loaded from global memory into registers while the current one feeds the
 // MFMAs, then written to the other buffer; one barrier per step.  LDS rows
 // are padded by 16 bytes so the 16-byte fragment reads of 32 consecutive
-// rows spread over the banks.  With F16 set, operand A may be stored as bf16
-// in memory and converted to fp16 as it is staged (CVT_A); bf16 values
-// convert exactly inside the fp16 normal range and saturate at +-65504.
+// rows spread over the banks.
 #pragma once
 #include "oc_device.h"
 
@@ -35,6 +33,7 @@ __device__ __forceinline__ uint16_t f2h_bits(float f) {
     return *reinterpret_cast<const uint16_t *>(&h);
 }
 
+// bf16 -> fp16: exact inside the fp16 normal range, saturating at +-65504
 __device__ __forceinline__ uint4 bf16x8_to_f16x8(uint4 v) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
     uint32_t o[4];
@@ -47,7 +46,7 @@ __device__ __forceinline__ uint4 bf16x8_to_f16x8(uint4 v) {
     return make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-template <int BA, int BB, int WA, int WB, bool F16 = false, bool CVT_A = false>
+template <int BA, int BB, int WA, int WB>
 struct MfmaTile {
     static constexpr int BK = 64;
     static constexpr int LDK = BK + 8;                 // padded LDS row (elements)
@@ -58,7 +57,6 @@ struct MfmaTile {
     static_assert(WA * WB == 4, "4 waves");
     static_assert(TA >= 1 && TB >= 1 && WTA % 32 == 0 && WTB % 32 == 0, "wave tile must be a multiple of 32");
     static_assert(CA >= 1 && CB >= 1, "tile too small for 256 threads");
-    static_assert(!CVT_A || F16, "conversion only towards fp16");
     static constexpr int BUF = (BA + BB) * LDK;        // elements per LDS buffer
     static constexpr size_t LDS_BYTES = (size_t)2 * BUF * 2;
 
@@ -68,7 +66,7 @@ struct MfmaTile {
     // the row base of chunk slot i (nullptr: zero row); rows are descriptors
     // of segments of seg_len elements, segment s at base + s * sub_stride
     // (seg_len == 0: one plain row).
-    template <bool CVT, int NC>
+    template <int NC>
     __device__ __forceinline__ static void load_step(const uint16_t *const *rows, int k0, int K, int seg_len,
                                                       long sub_stride, uint4 *regs) {
         const int kc = (threadIdx.x & 7) * 8;
@@ -85,7 +83,6 @@ struct MfmaTile {
                     p += k;
                 }
                 v = *reinterpret_cast<const uint4 *>(p);
-                if (CVT) v = bf16x8_to_f16x8(v);
             }
             regs[i] = v;
         }
@@ -109,33 +106,18 @@ struct MfmaTile {
         const int lr = lane & 31, lk = (lane >> 5) * 8;
 #pragma unroll
         for (int ks = 0; ks < BK; ks += 16) {
-            if constexpr (F16) {
-                f16x8 fa[TA], fb[TB];
+            bf16x8 fa[TA], fb[TB];
 #pragma unroll
-                for (int i = 0; i < TA; ++i)
-                    fa[i] = *reinterpret_cast<const f16x8 *>(As + (wa * WTA + i * 32 + lr) * LDK + ks + lk);
+            for (int i = 0; i < TA; ++i)
+                fa[i] = *reinterpret_cast<const bf16x8 *>(As + (wa * WTA + i * 32 + lr) * LDK + ks + lk);
 #pragma unroll
-                for (int j = 0; j < TB; ++j)
-                    fb[j] = *reinterpret_cast<const f16x8 *>(Bs + (wb * WTB + j * 32 + lr) * LDK + ks + lk);
+            for (int j = 0; j < TB; ++j)
+                fb[j] = *reinterpret_cast<const bf16x8 *>(Bs + (wb * WTB + j * 32 + lr) * LDK + ks + lk);
 #pragma unroll
-                for (int i = 0; i < TA; ++i)
-#pragma unroll
-                    for (int j = 0; j < TB; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-            } else {
-                bf16x8 fa[TA], fb[TB];
-#pragma unroll
-                for (int i = 0; i < TA; ++i)
-                    fa[i] = *reinterpret_cast<const bf16x8 *>(As + (wa * WTA + i * 32 + lr) * LDK + ks + lk);
+            for (int i = 0; i < TA; ++i)
 #pragma unroll
                 for (int j = 0; j < TB; ++j)
-                    fb[j] = *reinterpret_cast<const bf16x8 *>(Bs + (wb * WTB + j * 32 + lr) * LDK + ks + lk);
-#pragma unroll
-                for (int i = 0; i < TA; ++i)
-#pragma unroll
-                    for (int j = 0; j < TB; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-            }
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
         }
     }
 
@@ -151,17 +133,17 @@ struct MfmaTile {
             for (int j = 0; j < TB; ++j) acc[i][j] = f32x16{};
         const int nk = cdiv(K, BK);
         uint16_t *L0 = lds, *L1 = lds + BUF;
-        load_step<CVT_A, CA>(rowsA, 0, K, seg_len, sub_stride, ra0);
-        load_step<false, CB>(rowsB, 0, K, seg_len, sub_stride, rb0);
+        load_step<CA>(rowsA, 0, K, seg_len, sub_stride, ra0);
+        load_step<CB>(rowsB, 0, K, seg_len, sub_stride, rb0);
         store_step<CA>(L0, ra0);
         store_step<CB>(L0 + BA * LDK, rb0);
         if (nk > 1) {
-            load_step<CVT_A, CA>(rowsA, BK, K, seg_len, sub_stride, ra1);
-            load_step<false, CB>(rowsB, BK, K, seg_len, sub_stride, rb1);
+            load_step<CA>(rowsA, BK, K, seg_len, sub_stride, ra1);
+            load_step<CB>(rowsB, BK, K, seg_len, sub_stride, rb1);
         }
         if (nk > 2) {
-            load_step<CVT_A, CA>(rowsA, 2 * BK, K, seg_len, sub_stride, ra0);
-            load_step<false, CB>(rowsB, 2 * BK, K, seg_len, sub_stride, rb0);
+            load_step<CA>(rowsA, 2 * BK, K, seg_len, sub_stride, ra0);
+            load_step<CB>(rowsB, 2 * BK, K, seg_len, sub_stride, rb0);
         }
         __syncthreads();
         for (int kt = 0; kt < nk; kt += 2) {
@@ -172,8 +154,8 @@ struct MfmaTile {
                 store_step<CB>(L1 + BA * LDK, rb1);
             }
             if (kt + 3 < nk) {
-                load_step<CVT_A, CA>(rowsA, (kt + 3) * BK, K, seg_len, sub_stride, ra1);
-                load_step<false, CB>(rowsB, (kt + 3) * BK, K, seg_len, sub_stride, rb1);
+                load_step<CA>(rowsA, (kt + 3) * BK, K, seg_len, sub_stride, ra1);
+                load_step<CB>(rowsB, (kt + 3) * BK, K, seg_len, sub_stride, rb1);
             }
             __syncthreads();
             if (kt + 1 >= nk) break;
@@ -184,8 +166,8 @@ struct MfmaTile {
                 store_step<CB>(L0 + BA * LDK, rb0);
             }
             if (kt + 4 < nk) {
-                load_step<CVT_A, CA>(rowsA, (kt + 4) * BK, K, seg_len, sub_stride, ra0);
-                load_step<false, CB>(rowsB, (kt + 4) * BK, K, seg_len, sub_stride, rb0);
+                load_step<CA>(rowsA, (kt + 4) * BK, K, seg_len, sub_stride, ra0);
+                load_step<CB>(rowsB, (kt + 4) * BK, K, seg_len, sub_stride, rb0);
             }
             __syncthreads();
         }
