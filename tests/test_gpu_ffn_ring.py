@@ -19,6 +19,12 @@ pytestmark = pytest.mark.gpu
     (2304, 640, 2560, 1153),
     (1024, 64, 128, 77),         # one K step up, two down
     (64, 128, 64, 64),
+    (6000, 640, 1536, 6000),     # 256 x 192 up
+    (4000, 64, 3072, 4000),      # 128 x 192 up
+    (6000, 64, 1536, 6000),      # 160 x 128 up
+    (6000, 1536, 512, 6000),     # 256 x 192 down
+    (6000, 1536, 64, 6000),      # 160 x 128 down
+    (6000, 2048, 64, 6000),      # 128 x 192 down
 ])
 def test_ffn_ring(N, C, hidden, rows):
     if not torch.cuda.is_available():

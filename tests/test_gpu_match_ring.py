@@ -26,8 +26,9 @@ def gpu():
 @pytest.mark.parametrize("F,H,W,C,k", [
     (16, 72, 72, 128, 1),    # 256 x 256 tiles, six per block
     (4, 76, 78, 136, 1),     # 256 x 256, two per block
-    (5, 78, 72, 8, 1),       # 256 x 192, one K chunk
-    (5, 96, 64, 72, 1),      # 256 x 128, ragged last tile
+    (5, 78, 72, 8, 1),       # 128 x 128, one K chunk, several tiles per block
+    (5, 96, 64, 72, 1),      # 256 x 192, three per block
+    (3, 74, 88, 72, 1),      # 256 x 128, ragged last tile
     (5, 82, 78, 8, 1),       # 128 x 192
     (1, 66, 72, 8, 1),       # 96 x 128
     (2, 76, 70, 16, 1),      # 128 x 128
@@ -90,6 +91,7 @@ def test_frame_pairs(F, H, W, C, k, r_frame):
     (3, 32, 40, 128, 1),     # two, several representative tiles
     (5, 24, 16, 192, 2),     # three, patches
     (7, 64, 56, 64, 4),      # enough tiles that K is not split
+    (2, 72, 96, 128, 1),     # 96 x 128 tiles, three per block, two segments of two steps
 ])
 def test_blocks(F, H, W, C, k):
     print(f"blocks F={F} {H}x{W} C={C} k={k}", flush=True)

@@ -101,7 +101,7 @@ SMALL = [
          frame_drift=0.3),
     # degenerate grids: one 2x2 window (three candidates, one representative),
     # two frames (one candidate frame), and a bf16 channel count that is not a
-    # multiple of 64 (register-staged tiles instead of the DMA engine)
+    # multiple of 64
     dict(gran="token", F=1, H=2, W=2, C=16, heads=1, head_dim=16, dtype="bf16", r=0.5),
     dict(gran="frame", F=2, H=4, W=4, C=32, heads=2, head_dim=16, dtype="bf16", r_frame=0.6, planted=True),
     dict(gran="token", F=1, H=8, W=12, C=40, heads=1, head_dim=16, dtype="bf16", n_ctx=2),
@@ -159,7 +159,8 @@ def test_heavy_tailed_activations_chain(gran, head_dim, F, scale):
     # the other supported head dims, long and short sequences
     ("bf16", 32, 2, 1000, 0), ("bf16", 48, 3, 100, 0), ("bf16", 80, 2, 150, 0), ("bf16", 96, 2, 300, 0),
     ("bf16", 128, 3, 40, 0), ("bf16", 96, 1, 70, 3),
-    # K/V staged by DMA into padded K rows (head dims not a multiple of 64), ragged last tiles
+    # head dims not a multiple of 64, ragged last tiles
+    # (few query tiles: the keys shared out; larger grids of each head dim: test_gpu_flash_grids.py)
     ("bf16", 48, 2, 333, 0), ("bf16", 80, 1, 700, 0), ("bf16", 16, 2, 260, 0), ("bf16", 72, 1, 456, 4),
     # grids too large for eight-wave blocks: four-wave register staging for wide heads (O scaled in place,
     # V fragments per key block) and four-wave DMA for head dim 128 (K fragments read per tile)

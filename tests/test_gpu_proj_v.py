@@ -1,6 +1,6 @@
 """The V projection's transposed rows where tiles cross sequences (GPU,
 against the CPU oracle, OmniCache §3.2.3): sequence starts at every residue of
-4 and of 16, both tile engines, and the wide tiles."""
+4 and of 16, K tails, the wide tiles, and the key padding."""
 import numpy as np
 import pytest
 import torch
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dh,heads,C,n_seq,L", [
     (64, 2, 128, 5, 131),     # starts 0, 131, 262, ...: quads across sequences
-    (72, 1, 72, 3, 66),       # register-staged tiles (C not a multiple of 64), starts 2 mod 4
+    (72, 1, 72, 3, 66),       # K not a multiple of 64, starts 2 mod 4
     (32, 3, 64, 7, 100),      # starts 0 mod 4, not mod 16
     (64, 1, 64, 2, 272),      # starts 0 mod 16
     (64, 18, 64, 23, 133),    # 128 x 192 tiles (one round of them)

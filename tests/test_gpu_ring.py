@@ -1,7 +1,8 @@
 """Projections on the ring-buffered tiles (GPU, against the CPU oracle,
 OmniCache §3.2.3): a case per tile shape, K below the ring's depth and not a
 multiple of 64, ragged rows, context rows in the middle of an instruction's
-eight rows, listed rows, and V by rows for short sequences."""
+eight rows, listed rows, and V by rows for short sequences.  (The key padding
+after tiles of 96 and 160 rows: test_vt_padding.py.)"""
 import numpy as np
 import pytest
 import torch
@@ -30,6 +31,8 @@ pytestmark = pytest.mark.gpu
     (4, 64, 136, 1, 301, 33),      # the context starts inside an instruction's rows
     (2, 64, 64, 1, 0, 77),         # context rows only
     (16, 72, 72, 50, 40, 0),       # short sequences: V by rows
+    (8, 64, 1536, 60, 100, 0),     # 256 x 192 in the output projection
+    (8, 64, 3072, 20, 100, 0),     # 256 x 128
 ])
 def test_ring_shapes(heads, dh, C, n_seq, L, n_ctx):
     if not torch.cuda.is_available():
