@@ -41,9 +41,9 @@ PROFILES = {
 }
 PROFILE = PROFILES["sd3_1024"]
 _COMMON = ("oc_attn_common.h", "oc_device.h")
-_TILES = ("oc_ring_tile.h", "oc_dma_tile.h", "oc_mfma_tile.h", "oc_gemm_epi.h")
+_TILES = ("oc_ring_tile.h", "oc_mfma_tile.h", "oc_gemm_epi.h")
 KERNEL_SOURCES = {
-    "flash": ("k_flash.hip",) + _COMMON,
+    "flash": ("k_flash.hip", "k_flash_split.hip") + _COMMON,
     "proj_qkv": ("k_proj.hip",) + _TILES + _COMMON,
     "proj_out": ("k_proj.hip",) + _TILES + _COMMON,
     "match": ("k_match.hip", "oc_ring_tile.h", "oc_dma_tile.h", "oc_mfma_tile.h", "oc_groups.h", "oc_device.h"),
