@@ -314,11 +314,11 @@ __global__ __launch_bounds__(256) void k_match_mfma(const uint16_t *__restrict__
 // group's tiles for every group, in contiguous ranges per XCD, left the XCDs
 // whose range held few pairs idle for much of the launch.)
 //
-// Bounded by the MFMA rate at the clock the load leaves (248 of 288 us with
+// Bounded by the MFMA rate at the clock the load leaves (248 of 290 us with
 // the arg-max between the tiles reduced to a maximum).  Parts of one candidate
 // tile are adjacent, so they share its rows in one XCD's L2.  25 frames of 72
 // x 128 tokens of 320 channels, 5 pairs: 654 us on 128 x 128 tiles and the
-// full grid, 288 us this way; 12 pairs matched in 4 x 4 patches 91 -> 71;
+// full grid, 290 us this way; 12 pairs matched in 4 x 4 patches 91 -> 71;
 // 3072 x 1024 x 1536: 20.5 -> 19.8; 1024 tokens of C = 160 13.2 -> 8.4; blocks
 // of 25 frames of 320 channels, 16 groups of 432 x 144: 78 -> 62.
 template <int ID>
