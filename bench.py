@@ -93,7 +93,13 @@ def stage_work(shape, cfg, pl, n_ctx=0):
     rows = pl.n_kept + n_ctx
     lk = pl.seq_len + (n_ctx if pl.n_seq == 1 else 0)
     attn_flop = 4.0 * pl.n_seq * lk * lk * hd
-    S, D, G = pl.n_src_max, pl.n_dst_max, pl.n_groups
+    # candidates that exist: groups of a frame pair hold all tokens of two
+    # frame-patches but one's representatives, the others of one (n_src_max is
+    # the larger of the two)
+    n_cand, D = pl.n_groups * pl.n_src_max, pl.n_dst_max
+    if cfg.gran == "frame_token":
+        n = FN // shape.F
+        n_cand = (shape.F - 2 * pl.n_frame_cached) * (n - n // 4) + pl.n_frame_cached * (2 * n - n // 4)
     K = shape.F * C if cfg.gran == "block" else C
     frames = cfg.gran in ("frame", "frame_token")
     return {
@@ -102,7 +108,7 @@ def stage_work(shape, cfg, pl, n_ctx=0):
         "attn_short": (attn_flop, 2.0 * 4 * rows * hd),
         "qkv_attn_short": (2.0 * rows * C * 3 * hd + attn_flop, 2.0 * (rows * C + 3 * hd * C + rows * hd)),
         "proj_out": (2.0 * rows * hd * C, 2.0 * (rows * hd + hd * C + rows * C)),
-        "match": (2.0 * G * S * D * K, 2.0 * FN * C + 4.0 * FN),
+        "match": (2.0 * n_cand * D * K, 2.0 * FN * C + 4.0 * FN),
         "inv_norm": (2.0 * FN * C, 2.0 * FN * C + 4.0 * FN),
         "frame_gram": (2.0 * shape.F * shape.F * shape.N * C if frames else 0.0,
                        2.0 * FN * C + (4.0 * FN if cfg.gran == "frame_token" else 0.0)),

@@ -58,3 +58,17 @@ def test_stage_work_counts_sequences_apart_without_context():
     assert w["proj_qkv"][0] == 2.0 * 2048 * 1152 * 3 * 16 * 72
     assert w["match"][0] == 2.0 * 192 * 64 * 16 * 1152
     assert bench.roofline_of(*w["match"], 10.0)["bound"] == "hbm"              # 48 flop per byte
+
+
+@pytest.mark.parametrize("k", [1, 4])
+def test_stage_work_counts_the_candidates_that_exist(k):
+    # Frame+Token Cache: a pair's groups hold 2 n - n / 4 candidates (n tokens
+    # of a frame-patch), the other frames' n - n / 4, all beside n / 4
+    # representatives; the plan's n_src_max is the pairs' count for all
+    shape = oc.Shape(25, 72, 128, 320, 5, 64, 0, "bf16")
+    cfg = oc.Cfg("frame_token", r=0.5, r_frame=0.2, patch_k=k)
+    pl = oc.plan(shape, cfg)
+    n, pairs = 72 * 128 // k ** 2, pl.n_frame_cached
+    assert (pairs, pl.n_groups, pl.n_src_max) == (5, 20 * k * k, 2 * n - n // 4)
+    cand = k * k * (pairs * (2 * n - n // 4) + (25 - 2 * pairs) * (n - n // 4))
+    assert bench.stage_work(shape, cfg, pl)["match"][0] == 2.0 * cand * (n // 4) * 320
