@@ -1,5 +1,5 @@
-// Ring-buffered LDS-DMA MFMA tile engine for gfx950, one block per compute
-// unit: C[b][a] = sum_k A[a][k] * B[b][k] over a BA x BB tile, WA x WB waves,
+// Ring-buffered LDS-DMA MFMA tile engine for gfx950, one to three blocks per
+// compute unit: C[b][a] = sum_k A[a][k] * B[b][k] over a BA x BB tile, WA x WB waves,
 // 32x32 accumulators of v_mfma_f32_32x32x16_{bf16,f16}, K in steps of 64.
 //
 // What bounds a projection here: a step moves (BA + BB) x 128 bytes from L2 to
